@@ -81,10 +81,12 @@ constexpr double kF32Rho2 = 0.5;
 // pass skips, and the sweep that would show the stall is saved).
 constexpr double kF32Tol2 = 0x1p-30;
 
-// Smallest n whose FP64 Jacobi phase runs on several workgroups by default (MI355X, per
-// rotation, one workgroup against several: n = 512 3.77 / 4.10 us, 1024 5.02 / 4.29,
-// 2048 7.23 / 4.77, 4096 11.52 / 5.37; the two cross near n = 670).
-constexpr int kMultiWgMinN = 768;
+// Smallest n whose FP64 Jacobi phase runs on several workgroups by default, with one rotation
+// per exchange (MI355X, per rotation, one workgroup against several: n = 512 3.77 / 4.10 us,
+// 1024 5.02 / 4.29, 2048 7.23 / 4.77, 4096 11.52 / 5.37; the two cross near n = 670) and with
+// speculative rounds, where the scores of a round load one workgroup's SIMDs earlier (n = 400
+// 2.36 / 2.36 us, 512 2.57 / 2.36, 600 with a tight cluster 4.50 / 3.52, 1024 3.70 / 2.23).
+constexpr int kMultiWgMinN = 768, kMultiWgMinNSpec = 400;
 
 // Range of the entries solved as given: outside it the input is scaled by a power of two
 // (exact) so that squares in FP64 and the FP32 copy of the preconditioner stay in range.
@@ -371,7 +373,9 @@ int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, d
   const bool mirror = o.update_mode != 2;  // one problem: mirror mode unless asked otherwise
   // several workgroups for large HBM-resident problems (mirror mode, no phase timers)
   bool multi = !lds && mirror &&
-               (o.jacobi_wgs == 2 || (o.jacobi_wgs == 0 && n >= kMultiWgMinN));
+               (o.jacobi_wgs == 2 ||
+                (o.jacobi_wgs == 0 &&
+                 n >= (jacobi_speculates(pivot, o.stop) ? kMultiWgMinNSpec : kMultiWgMinN)));
   long long base_rot = 0;
   JCtl hc{};
   float ms_apply = 0.f;
@@ -414,7 +418,7 @@ int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, d
   S.ms_jacobi_kernel = ms_kernel;
   S.ms_apply_log = ms_apply;
   int rows_per_thread = 0;
-  if (multi) mw_shape(n, &S.jacobi_wgs, &rows_per_thread);
+  if (multi) mw_shape(n, jacobi_speculates(pivot, o.stop), &S.jacobi_wgs, &rows_per_thread);
   else S.jacobi_wgs = 1;
   S.rotations = hc.rotations;
   S.rescans = hc.rescans;
@@ -1020,8 +1024,8 @@ struct Cohort {
       for (int shp : shapes) {
         HIPCHK(launch_zero_words(d_cnt, 2, s));
         Timer tt(s);
-        HIPCHK(launch_jacobi_queue(dm, d_idx_lds, (int)smp.size(), nmx, pivot, lds, mirror,
-                                   shp, d_cnt, queue_grid(lds, shp, smp.size()), s));
+        HIPCHK(launch_jacobi_queue(dm, d_idx_lds, (int)smp.size(), nmx, pivot, o.stop, lds,
+                                   mirror, shp, d_cnt, queue_grid(lds, shp, smp.size()), s));
         const float ms = tt.stop();
         if (shp == a) { t_default = ms; t_best = ms; *shape = a; }
         else if (ms < 0.95f * t_default && ms < t_best) { t_best = ms; *shape = shp; }
@@ -1185,11 +1189,11 @@ struct Cohort {
           auto queue = [&]() -> hipError_t {
             hipError_t e = launch_zero_words(d_cnt, 2, s);
             if (e == hipSuccess && !il.empty())
-              e = launch_jacobi_queue(dm, d_idx_lds, (int)il.size(), nl, pivot, true, mirror,
-                                      shape_lds, d_cnt, gl, s);
+              e = launch_jacobi_queue(dm, d_idx_lds, (int)il.size(), nl, pivot, o.stop, true,
+                                      mirror, shape_lds, d_cnt, gl, s);
             if (e == hipSuccess && !ih.empty())
-              e = launch_jacobi_queue(dm, d_idx_hbm, (int)ih.size(), nh, pivot, false, mirror,
-                                      shape_hbm, d_cnt + 1, gh, s);
+              e = launch_jacobi_queue(dm, d_idx_hbm, (int)ih.size(), nh, pivot, o.stop, false,
+                                      mirror, shape_hbm, d_cnt + 1, gh, s);
             return e;
           };
           if (!o.graph) {
@@ -1200,10 +1204,10 @@ struct Cohort {
             // kernel attributes (the LDS size) are set outside the capture: grid 0 only
             // prepares the launch
             if (!il.empty())
-              HIPCHK(launch_jacobi_queue(dm, d_idx_lds, (int)il.size(), nl, pivot, true, mirror,
-                                         shape_lds, d_cnt, 0, s));
+              HIPCHK(launch_jacobi_queue(dm, d_idx_lds, (int)il.size(), nl, pivot, o.stop, true,
+                                         mirror, shape_lds, d_cnt, 0, s));
             if (!ih.empty())
-              HIPCHK(launch_jacobi_queue(dm, d_idx_hbm, (int)ih.size(), nh, pivot, false,
+              HIPCHK(launch_jacobi_queue(dm, d_idx_hbm, (int)ih.size(), nh, pivot, o.stop, false,
                                          mirror, shape_hbm, d_cnt + 1, 0, s));
             if (int r = capture(&g_jq, queue)) return r;
             if (int r = capture(&g_ja, [&]() -> hipError_t {

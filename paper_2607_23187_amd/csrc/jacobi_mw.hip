@@ -25,64 +25,17 @@
 // wait is bounded; a wait that runs out sets an abort flag that ends all workgroups.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "jacobi_device.h"
+#include "jacobi_spec.h"
 #include "kernels.h"
+#include "mw_exchange.h"
 
 namespace je {
 
-constexpr int kMwStride = 8;            // XCDs: workgroup i runs on XCD i % 8
-constexpr int kMwSpinLimit = 1 << 22;   // polls of one wait before it gives up
 constexpr int kMwWords = 28;            // words of one workgroup's slot: 6 candidates x 4 + 3 sums
-
-__device__ __forceinline__ double ld_ag(const double* p) {
-  const unsigned long long v = __hip_atomic_load(
-      reinterpret_cast<unsigned long long*>(const_cast<double*>(p)), __ATOMIC_RELAXED,
-      __HIP_MEMORY_SCOPE_AGENT);
-  return __longlong_as_double((long long)v);
-}
-
-// Stores need only reach the L2 that every workgroup of the launch shares (they all run on
-// one XCD, checked at the start): workgroup-scope stores are acknowledged there, without
-// the write-through of device-scope ones (measured 0.81 against 1.08 us per exchange round
-// for 16 workgroups).  Readers use agent-scope loads, which miss their own CU's cache.
-__device__ __forceinline__ void st_ag(double* p, double v) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
-                     (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ int ld_ag_i(int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void st_ag_i(int* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Arrival of this workgroup at exchange round `round` (1-based) and the wait for all G.
-// False when the wait ran out or another workgroup gave up (the abort flag is then set).
-__device__ __forceinline__ bool mw_sync(MwCtl* mc, int G, int round) {
-  int ok = 1;
-  // this wave's stores (its slot and its part of A) have been acknowledged by L2; the
-  // compiler fences keep every memory access of the round on its side of the barrier
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0);
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(&mc->counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int target = G * round;
-    int spins = 0;
-    while (ld_ag_i(&mc->counter) < target) {
-      if (++spins > kMwSpinLimit || ld_ag_i(&mc->abort)) {
-        st_ag_i(&mc->abort, 1);
-        ok = 0;
-        break;
-      }
-    }
-  }
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  return __builtin_amdgcn_readfirstlane(ok) != 0;
-}
 
 // A candidate as four words of a slot: score, value, bound, and (row | flag << 31,
 // column) as two 32-bit halves (row and column are non-negative ints).
@@ -126,22 +79,8 @@ __global__ __launch_bounds__(64) void k_jacobi_mw(JDesc d, long long log_base, M
   auto ld_a = [&](int r, int c) -> double { return ld_ag(gA + (size_t)r * ld + c); };
   auto st_a = [&](int r, int c, double v) { st_ag(gA + (size_t)r * ld + c, v); };
 
-  // ---- start: every workgroup on one XCD, all of them resident
   int round = 1;
-  if (lane == 0) st_ag_i(&mc->xcc[g], __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 0xf);
-  if (!mw_sync(mc, G, round)) {
-    // not all resident: nothing touched yet, the host falls back
-    if (lane == 0) st_ag_i(&mc->misplaced, 1);
-    return;
-  }
-  {
-    const int x0 = ld_ag_i(&mc->xcc[0]);
-    const int xi = lane < G ? ld_ag_i(&mc->xcc[lane]) : x0;
-    if (__ballot(xi != x0)) {
-      if (g == 0 && lane == 0) st_ag_i(&mc->misplaced, 1);
-      return;
-    }
-  }
+  if (!mw_start(mc, G, g, round)) return;
 
   // ---- per-thread rows k = T + i GT; the whole diagonal in LDS
   double dk[RM], bs[RM], bv[RM], bu[RM], cb[RM], cu[RM], of2[RM];
@@ -432,11 +371,142 @@ __global__ __launch_bounds__(64) void k_jacobi_mw(JDesc d, long long log_base, M
   }
 }
 
-// Workgroups and rows per thread for n: G = min(32, ceil(n / 64)) one-wave workgroups, RM
-// rows per thread (1, 2 or 4).
-void mw_shape(int n, int* G, int* RM) {
+// ------------------------------------------------------------------ speculative rounds
+// The exchange of the speculative loop (jacobi_spec.h) between G one-wave workgroups.  A
+// round costs two waits: one on the slots of candidates (publishing, store acknowledgements,
+// counter barrier, slot read), one on the vote.  The vote is a single 64-bit atomic per
+// workgroup, which carries the arrival and the first stage it could not prove: arrivals in
+// the low byte, six bits per stage above it (at most 32 workgroups each).
+template <bool GAP_>
+struct MwExchange {
+  static constexpr bool kExchange = true;
+  static constexpr int kSlotWords = 2 * kMwMaxGroups * 4 * 4;  // two rounds, four a workgroup
+  MwCtl* mc;
+  double* xb;
+  double* A;
+  double* s_diag;
+  int G, g, T, GT, ld_, lane, round, votes;
+  bool alive;
+
+  __device__ __forceinline__ bool first_wave() const { return g == 0; }
+  __device__ __forceinline__ bool ok() const { return alive; }
+  __device__ __forceinline__ double* slot(int b, int idx) const {
+    return xb + (size_t)(b * kMwMaxGroups * 4 + idx) * 4;
+  }
+  __device__ __forceinline__ void publish(bool win, const SCand& x) {
+    if (win) {
+      double* p = slot((round + 1) & 1, 4 * g + (lane >> 4));
+      st_ag(p, x.s);
+      st_ag(p + 1, x.a);
+      st_ag(p + 2, __longlong_as_double((long long)x.rc));
+    }
+  }
+  __device__ __forceinline__ SCand gather(const SCand&) {
+    ++round;
+    alive = mw_sync(mc, G, round);
+    SCand y = empty_scand();
+    if (!alive) return y;
+    SCand z[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      z[u] = empty_scand();
+      if (u * 16 < G && lane + 64 * u < 4 * G) {
+        const double* p = slot(round & 1, lane + 64 * u);
+        z[u].s = ld_ag(p);
+        z[u].a = ld_ag(p + 1);
+        z[u].rc = (int)__double_as_longlong(ld_ag(p + 2));
+      }
+    }
+    int yk = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int zk = scand_key(z[u].rc);
+      if (z[u].s >= 0.0 && better(z[u].s, zk, y.s, yk)) { y = z[u]; yk = zk; }
+    }
+    return y;
+  }
+  // Words of the vote are used in turn; the word two votes ahead, which every workgroup has
+  // left, is cleared here and acknowledged before the next candidates' barrier.
+  __device__ __forceinline__ int vote(int F, int kk) {
+    if (kk == 1) return 1;
+    // the loads of this round are complete: after the vote other workgroups store into the
+    // rows they came from
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    unsigned long long* word = &mc->vote[votes & 3];
+    if (lane == 0) {
+      unsigned long long add = 1;
+      if (F < kk) add |= 1ull << (8 + 7 * (F - 1));
+      __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    unsigned long long v = 0;
+    int spins = 0;
+    for (;;) {
+      v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((int)(v & 0xff) >= G) break;
+      if (++spins > kMwSpinLimit || (!(spins & 63) && ld_ag_i(&mc->abort))) {
+        if (lane == 0) st_ag_i(&mc->abort, 1);
+        alive = false;
+        return 0;
+      }
+    }
+    if (g == 0 && lane == 0)
+      __hip_atomic_store(&mc->vote[(votes + 2) & 3], 0ull, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    ++votes;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    const unsigned long long fails = v >> 8;
+    return __builtin_amdgcn_readfirstlane(fails ? (__ffsll((long long)fails) - 1) / 7 + 1 : kk);
+  }
+  __device__ __forceinline__ Cand best(const Cand& x) {
+    ++round;
+    double* my = xb + kSlotWords + (size_t)((round & 1) * G + g) * 4;
+    if (lane == 0) put_cand(my, x);
+    alive = mw_sync(mc, G, round);
+    Cand y = empty_cand();
+    if (!alive) return y;
+    if (lane < G)
+      y = get_cand(xb + kSlotWords + (size_t)((round & 1) * G + lane) * 4);
+    Cand e1 = empty_cand(), e2 = empty_cand();
+    wave_best3(e1, 0, y, y.c, e2, 0);
+    return y;
+  }
+  __device__ __forceinline__ double ld(int r, int k, int) const {
+    return ld_ag(A + (size_t)r * ld_ + k);
+  }
+  __device__ __forceinline__ double ld2(int r, int l) const { return ld_ag(A + (size_t)r * ld_ + l); }
+  __device__ __forceinline__ void st(int r, int k, double v) { st_ag(A + (size_t)r * ld_ + k, v); }
+  __device__ __forceinline__ void stm(int k, int r, double v) { st_ag(A + (size_t)k * ld_ + r, v); }
+  __device__ __forceinline__ double diag(int k) const { return s_diag[k]; }
+  __device__ __forceinline__ void set_diag(int p, int q, double dp, double dq, int) {
+    s_diag[p] = dp;
+    s_diag[q] = dq;
+  }
+};
+
+template <int RM, int K, bool GAP>
+__global__ __launch_bounds__(64) void k_jacobi_spec_mw(JDesc d, long long log_base, MwCtl* mc,
+                                                       double* xb, int G) {
+  if (blockIdx.x % kMwStride) return;
+  const int g = blockIdx.x / kMwStride;
+  if (g >= G) return;
+  extern __shared__ double s_diag[];
+  const int lane = threadIdx.x;
+  int round = 1;
+  if (!mw_start(mc, G, g, round)) return;
+  for (int l = lane; l < d.n; l += kWave) s_diag[l] = d.diag[l];
+  __syncthreads();
+  MwExchange<GAP> ex{mc, xb, d.A, s_diag, G, g, g * kWave + lane, G * kWave, d.ld, lane,
+                     round, 0, true};
+  spec_loop<RM, K, GAP>(d, log_base, ex);
+}
+
+// Workgroups and rows per thread for n: G = ceil(n / 64) one-wave workgroups, at most 32 (one
+// per CU of an XCD) for one rotation per exchange and 64 for speculative rounds, where the
+// scores of a round bound the wave; RM rows per thread (1, 2 or 4).
+void mw_shape(int n, bool spec, int* G, int* RM) {
   int g = (n + kWave - 1) / kWave;
-  if (g > kMwMaxGroups) g = kMwMaxGroups;
+  g = std::min(g, spec ? kMwMaxGroups : kMwMaxGroups / 2);
   int rm = (n + g * kWave - 1) / (g * kWave);
   if (rm == 3) rm = 4;
   *G = g;
@@ -444,16 +514,23 @@ void mw_shape(int n, int* G, int* RM) {
 }
 
 size_t mw_bytes(int n) {
-  int G, RM;
-  mw_shape(n, &G, &RM);
-  return sizeof(MwCtl) + (size_t)2 * G * kMwWords * sizeof(double);
+  int G, RM, Gs;
+  mw_shape(n, false, &G, &RM);
+  mw_shape(n, true, &Gs, &RM);
+  const size_t one = (size_t)2 * G * kMwWords;  // one rotation per exchange
+  const size_t spec = MwExchange<true>::kSlotWords + (size_t)2 * Gs * 4;
+  return sizeof(MwCtl) + std::max(one, spec) * sizeof(double);
 }
 
+// The speculative loop covers every case but two, whose stop rules need more than the best
+// pivot after each rotation: the off-norm stop, and greedy pivots with the certificate.
 template <int RM, bool GAP>
 static hipError_t launch_mw_t(const JDesc& d, long long log_base, int G, MwCtl* mc, double* xb,
                               hipStream_t s) {
   const size_t sh = (size_t)d.n * sizeof(double);
   auto fn = k_jacobi_mw<RM, GAP>;
+  if constexpr (RM <= 2)
+    if (jacobi_speculates(d.pivot, d.stop)) fn = k_jacobi_spec_mw<RM, RM == 1 ? 8 : 4, GAP>;
   if (sh > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)fn,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
@@ -467,7 +544,7 @@ static hipError_t launch_mw_t(const JDesc& d, long long log_base, int G, MwCtl* 
 
 hipError_t launch_jacobi_mw(const JDesc& d, long long log_base, void* buf, hipStream_t s) {
   int G, RM;
-  mw_shape(d.n, &G, &RM);
+  mw_shape(d.n, jacobi_speculates(d.pivot, d.stop), &G, &RM);
   // every row needs an owner thread
   if ((long long)G * kWave * RM < d.n || G > kMwMaxGroups) return hipErrorInvalidValue;
   MwCtl* mc = (MwCtl*)buf;

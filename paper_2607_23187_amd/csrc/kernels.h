@@ -65,6 +65,10 @@ hipError_t launch_get_diag(const double* A, int n, int ld, double* diag, hipStre
 hipError_t launch_jacobi(const JDesc& d, long long log_base, bool lds_mode, bool mirror,
                          hipStream_t s);
 bool jacobi_fits_lds(int n);
+// true when the loop may perform several rotations per exchange (jacobi_spec.h)
+inline bool jacobi_speculates(int pivot, int stop) {
+  return stop != STOP_OFF && (pivot == 1 || stop == STOP_SCORE);
+}
 // V[i][:] <- V[i][:] * G_1 ... G_m for every row (rotations of `log`, in order).
 hipError_t launch_apply_log(double* V, int n, int ldv, const RotEntry* log, long long m,
                             hipStream_t s);
@@ -74,15 +78,16 @@ hipError_t launch_apply_log(double* V, int n, int ldv, const RotEntry* log, long
 // block and the exchange area (mw_bytes(n) bytes).  After the launch, MwCtl::misplaced = 1
 // means the kernel returned without touching the state (run launch_jacobi instead);
 // abort = 1 without it means a wait ran out mid-run (device error).
-constexpr int kMwMaxGroups = 32;
-struct MwCtl {
+constexpr int kMwMaxGroups = 64;
+struct alignas(8) MwCtl {
   int counter;                // arrivals at the exchange barriers
-  int abort;                  // a wait ran out
+  int abort;                  // a wait ran out (read together with the counter)
   int misplaced;              // the workgroups were not all resident on one XCD
   int pad;
   int xcc[kMwMaxGroups];      // XCC id of every workgroup
+  unsigned long long vote[4]; // votes of the speculative rounds, used in turn
 };
-void mw_shape(int n, int* G, int* RM);
+void mw_shape(int n, bool spec, int* G, int* RM);
 size_t mw_bytes(int n);
 hipError_t launch_jacobi_mw(const JDesc& d, long long log_base, void* buf, hipStream_t s);
 hipError_t launch_set_identity(double* V, int n, int ldv, hipStream_t s);
@@ -187,7 +192,7 @@ hipError_t launch_init_rows_b(BMat* m, int count, int nmax, int pivot, int use_c
 // taken from a device counter in the given order); lds_mode as for launch_jacobi.  With
 // grid <= 0 only the kernel's attributes are set (before a graph capture).
 hipError_t launch_jacobi_queue(BMat* m, const int* idx, int count, int nmax, int pivot,
-                               bool lds_mode, bool mirror, int threads, int* counter, int grid,
+                               int stop, bool lds_mode, bool mirror, int threads, int* counter, int grid,
                                hipStream_t s);
 hipError_t launch_apply_log_b(BMat* m, int count, int nmax, hipStream_t s);
 hipError_t launch_sort_output_b(BMat* m, int count, int nmax, int sort, hipStream_t s);
