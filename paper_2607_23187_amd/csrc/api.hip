@@ -480,6 +480,8 @@ int svd_one(const double* B, int m, int n, int ldb, double* S, double* U, int ld
   size_t bytes = 2 * ym + 2 * mat + 5 * al((size_t)n * 8) + 3 * al((size_t)n * 4) + al(64) +
                  al(sizeof(JCtl));
   if (pre) bytes += 5 * mat + al(precond_f32_bytes(n));
+  const size_t mwb = svd_mw_bytes(m, n);
+  bytes += al(mwb);
   int err = JE_OK;
   char* p = (char*)pool_get(bytes, &err);
   if (!p) return err;
@@ -508,6 +510,7 @@ int svd_one(const double* B, int m, int n, int ldb, double* S, double* U, int ld
     A = (double*)take(mat);
     f32 = take(precond_f32_bytes(n));
   }
+  void* mw = mwb ? take(mwb) : nullptr;
   je_stats Sx{};
 
   // ---- 1. B row-major, finiteness, A = B^T B, ||A||_F
@@ -560,7 +563,17 @@ int svd_one(const double* B, int m, int n, int ldb, double* S, double* U, int ld
   d.plog = o.pivot_log; d.logcap = o.pivot_log ? o.pivot_log_cap : 0;
   d.ctl = ctl;
   HIPCHK(hipMemsetAsync(ctl, 0, sizeof(JCtl), s));
-  HIPCHK(launch_svd_jacobi(d, s));
+  bool multi = mw != nullptr;
+  if (multi) {
+    MwCtl mc{};
+    HIPCHK(launch_svd_mw(d, mw, s));
+    HIPCHK(hipMemcpyAsync(&mc, mw, 16, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    // not all resident on one XCD: nothing touched, the one-workgroup kernel takes over
+    if (mc.misplaced) multi = false;
+    else if (mc.abort) return JE_ERR_DEVICE;
+  }
+  if (!multi) HIPCHK(launch_svd_jacobi(d, s));
   JCtl hc{};
   HIPCHK(hipMemcpyAsync(&hc, ctl, sizeof(JCtl), hipMemcpyDeviceToHost, s));
   Sx.ms_jacobi = tj.stop();

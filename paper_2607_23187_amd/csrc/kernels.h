@@ -309,6 +309,12 @@ hipError_t launch_svd_transpose(const double* Q, int ldq, int n, double* Vt, int
 hipError_t launch_svd_jacobi(const SDesc& d, hipStream_t s);
 // true when B and the per-row state of the rotation kernel fit in LDS
 bool svd_resident(int m, int n);
+// The same on several workgroups of one XCD, each with a slice of B in LDS.  `buf`:
+// svd_mw_bytes(m, n) bytes (0: this shape runs on one workgroup); it starts with an MwCtl,
+// whose misplaced and abort read as for launch_jacobi_mw.
+constexpr int kSvdMwGroups = 32;
+size_t svd_mw_bytes(int m, int n);
+hipError_t launch_svd_mw(const SDesc& d, void* buf, hipStream_t s);
 hipError_t launch_svd_out(const double* Y, int ldy, int m, const double* G, int ldg,
                           const double* Vt, int ldvt, int n, int* rank, double* S, double* U,
                           int ldu, double* V, int ldv, hipStream_t s);

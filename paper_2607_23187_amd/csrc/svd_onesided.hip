@@ -8,16 +8,19 @@
 // after a rotation of columns p and q the rows p and q of A are recomputed.  With
 // -ffp-contract=off every value is then a function of the input bits alone.
 //
-// One persistent workgroup runs the whole rotation sequence.  When B and the per-row state
-// fit, B lives in LDS for the whole run (written back at the end); otherwise it stays in
-// HBM.  Per rotation:
+// One persistent launch runs the whole rotation sequence: one workgroup with B in LDS when it
+// and the per-row state fit, several workgroups with a slice of B each above that, one
+// workgroup with B in HBM beyond what 32 slices hold.  With one workgroup, per rotation:
 //   argmax over the per-row best scores (each wave redundantly: no cross-wave exchange),
 //   rotation of columns p, q of B and of rows p, q of the right factor V^T, barrier,
 //   the dot products of rows p and q of A, barrier,
 //   per-row cache refresh (Sec. 3.2), rows needing a full rescan queued in LDS, barrier,
 //   full rescans, one wave per queued row, barrier.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
+#include "mw_exchange.h"
 
 namespace je {
 
@@ -150,6 +153,19 @@ __global__ __launch_bounds__(256) void k_svd_transpose(const double* __restrict_
   const int k = blockIdx.y;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256)
     Vt[(size_t)k * ldv + i] = Q[(size_t)i * ldq + k];
+}
+
+// Yc[k][r] = Y[r][k] (32 x 32 tiles through LDS): B column by column.
+__global__ __launch_bounds__(256) void k_svd_columns(const double* __restrict__ Y, int ldy, int m,
+                                                     int n, double* __restrict__ Yc, int ldc) {
+  __shared__ double t[32][33];
+  const int r0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int j = ty; j < 32; j += 8)
+    if (r0 + j < m && k0 + tx < n) t[j][tx] = Y[(size_t)(r0 + j) * ldy + k0 + tx];
+  __syncthreads();
+  for (int j = ty; j < 32; j += 8)
+    if (k0 + j < n && r0 + tx < m) Yc[(size_t)(k0 + j) * ldc + r0 + tx] = t[tx][j];
 }
 
 // ------------------------------------------------------------------ the rotation sequence
@@ -605,6 +621,349 @@ __global__ __launch_bounds__(NT) void k_svd1(const SDesc d) {
   }
 }
 
+// ------------------------------------------------------------------ several workgroups
+// B too large for one LDS: G workgroups on one XCD hold c columns of it each, in LDS for the
+// whole run.  A column-major copy of B in device memory carries the columns between them.
+// Per rotation every workgroup
+//   loads the old columns p, q (L2), rotates them into LDS (the owners also store them);
+//   forms the dot products of its columns with the new p and q, one lane each in index order,
+//   and those of p and q with themselves;
+//   stores its entries of A (rows and columns p, q), refreshes the caches of its rows, rescans
+//   those whose best moved down, and finds its part of the new rows' bests;
+//   exchanges its best row and those two, after which all hold the same winner.
+// Bound: the dot products (dot_in_order), then the exchange (0.6 us) and the L2 reads of the
+// columns and of the rows rescanned.  One workgroup alone read all of B from L2 at 22 GB/s per
+// rotation: 1024 x 512 186 -> 17 us per rotation, 300 x 260 38.8 -> 9.5, 130 x 129 13.4 -> 6.6.
+constexpr int kSvdMwThreads = 256;
+constexpr int kSvdMwWords = 9;  // three candidates: score, entry, row << 32 | column
+
+// Row stride of the LDS columns: even (16-byte loads) and 4 banks apart from column to column.
+__host__ __device__ __forceinline__ int svd_mw_stride(int m) { return (m + 31) / 32 * 32 + 2; }
+
+__host__ __device__ __forceinline__ size_t svd_mw_lds(int m, int n, int c) {
+  return 8 * ((size_t)(c + 2) * svd_mw_stride(m) + n + 4 * (size_t)c) + 8 * (size_t)c;
+}
+
+// sum_i u_i y_i in index order, 16 elements in flight ahead of the sums.  What bounds it is the
+// LDS return path of the one wave (both factors, 16 bytes a lane in 21 cycles; the chain of
+// additions alone takes 8 cycles a step); handing u round a row of lanes on the DPP network
+// instead of reading it measured slower (1009 x 33: 18.7 against 17.2 us per rotation).
+__device__ __forceinline__ double dot_in_order(const double* u, const double* y, int m) {
+  constexpr int kB = 16;
+  double x = 0.0;
+  int i = 0;
+  if (m >= 2 * kB) {
+    double pr[kB];
+    double2 a[kB / 2], b[kB / 2];
+#pragma unroll
+    for (int e = 0; e < kB / 2; ++e) {
+      const double2 v = *reinterpret_cast<const double2*>(u + 2 * e);
+      const double2 w = *reinterpret_cast<const double2*>(y + 2 * e);
+      pr[2 * e] = v.x * w.x;
+      pr[2 * e + 1] = v.y * w.y;
+      a[e] = *reinterpret_cast<const double2*>(u + kB + 2 * e);
+      b[e] = *reinterpret_cast<const double2*>(y + kB + 2 * e);
+    }
+    // pr: products of block [i - 2 kB, i - kB); a, b: operands of [i - kB, i)
+    for (i = 2 * kB; i + kB <= m; i += kB) {
+#pragma unroll
+      for (int e = 0; e < kB / 2; ++e) {
+        x += pr[2 * e];
+        pr[2 * e] = a[e].x * b[e].x;
+        x += pr[2 * e + 1];
+        pr[2 * e + 1] = a[e].y * b[e].y;
+        a[e] = *reinterpret_cast<const double2*>(u + i + 2 * e);
+        b[e] = *reinterpret_cast<const double2*>(y + i + 2 * e);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < kB; ++e) x += pr[e];
+#pragma unroll
+    for (int e = 0; e < kB / 2; ++e) {
+      x += a[e].x * b[e].x;
+      x += a[e].y * b[e].y;
+    }
+  }
+  for (; i < m; ++i) x += u[i] * y[i];
+  return x;
+}
+
+// (score, column) maximum of a wave's lanes with its entry, every lane the result.
+struct SvdBest {
+  double v, a;
+  int c;
+};
+
+__device__ __forceinline__ SvdBest wave_svd_best(double v, int c, double a) {
+  const int w = wave_argmax_lane(v, c);
+  if (w < 0) return SvdBest{-1.0, 0.0, INT_MAX};
+  return SvdBest{readlane_d(v, w), readlane_d(a, w), readlane_i(c, w)};
+}
+
+template <int PIV>
+__global__ __launch_bounds__(kSvdMwThreads) void k_svd_mw(const SDesc d, MwCtl* mc, double* xb,
+                                                          double* Yc, int ldc, int G, int c) {
+  if (blockIdx.x % kMwStride) return;
+  const int g = blockIdx.x / kMwStride;
+  if (g >= G) return;
+  constexpr int NT = kSvdMwThreads, NW = NT / 64;
+  extern __shared__ __align__(16) double smem[];
+  __shared__ int s_cnt, s_ok, s_rc[3];
+  __shared__ double s_best[3], s_val[3], s_new[2];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = d.n, m = d.m, S = svd_mw_stride(m);
+  const int k0 = g * c, nk = min(c, n - k0);
+  const size_t ldg = d.ldg, ldv = d.ldv;
+  double* Ys = smem;
+  double* colp = Ys + (size_t)c * S;
+  double* colq = colp + S;
+  double* diag = colq + S;
+  double* best = diag + n;
+  double* val = best + c;
+  double* xp = val + c;
+  double* xq = xp + c;
+  int* arg = (int*)(xq + c);
+  int* list = arg + c;
+
+  int round = 1;
+  if (wv == 0) {
+    const bool ok = mw_start(mc, G, g, round);
+    if (lane == 0) s_ok = ok;
+  }
+  __syncthreads();
+  if (!s_ok) return;
+
+  for (int k = 0; k < nk; ++k)
+    for (int i = tid; i < m; i += NT) Ys[(size_t)k * S + i] = Yc[(size_t)(k0 + k) * ldc + i];
+  for (int k = tid; k < n; k += NT) diag[k] = d.diag[k];
+  for (int k = tid; k < nk; k += NT) {
+    best[k] = d.best[k0 + k];
+    const int a = d.arg[k0 + k];
+    arg[k] = a;
+    val[k] = a >= 0 ? d.G[(size_t)(k0 + k) * ldg + a] : 0.0;
+  }
+  if (tid == 0) s_cnt = 0;
+  __syncthreads();
+
+  long long rot = 0, resc = 0;
+  int status = ST_OK, p = -1, q = -1;
+  double vsel = -1.0;
+  bool failed = false;
+  // this lane's part of the new rows p and q (wave 0)
+  double vp = -1.0, ap = 0.0, vq = -1.0, aq = 0.0;
+  int cp = INT_MAX, cq = INT_MAX;
+  for (;;) {
+    // ---- exchange: wave 0 publishes and reads, the others wait
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have reached L2
+    __syncthreads();
+    ++round;
+    if (wv == 0) {
+      double v = -1.0, a = 0.0;
+      int r = INT_MAX, rc = 0;
+      for (int k = lane; k < nk; k += 64) {
+        if (k0 + k == p || k0 + k == q) continue;
+        if (best[k] > v) { v = best[k]; r = k0 + k; rc = arg[k]; a = val[k]; }
+      }
+      const int w = wave_argmax_lane(v, r);
+      const SvdBest bp = wave_svd_best(vp, cp, ap), bq = wave_svd_best(vq, cq, aq);
+      double* my = xb + (size_t)((round & 1) * G + g) * kSvdMwWords;
+      if (lane == (w < 0 ? 0 : w)) {
+        st_ag(my, w < 0 ? -1.0 : v);
+        st_ag(my + 1, a);
+        st_ag(my + 2, __longlong_as_double((long long)r << 32 | (unsigned)rc));
+      }
+      if (lane == 0) {
+        st_ag(my + 3, bp.v);
+        st_ag(my + 4, bp.a);
+        st_ag(my + 5, __longlong_as_double((long long)bp.c));
+        st_ag(my + 6, bq.v);
+        st_ag(my + 7, bq.a);
+        st_ag(my + 8, __longlong_as_double((long long)bq.c));
+      }
+      const bool ok = mw_sync(mc, G, round);
+      double s1 = -1.0, a1 = 0.0, s2 = -1.0, a2 = 0.0, s3 = -1.0, a3 = 0.0;
+      long long i1 = 0, i2 = 0, i3 = 0;
+      if (ok && lane < G) {
+        const double* sl = xb + (size_t)((round & 1) * G + lane) * kSvdMwWords;
+        s1 = ld_ag(sl); a1 = ld_ag(sl + 1); i1 = __double_as_longlong(ld_ag(sl + 2));
+        s2 = ld_ag(sl + 3); a2 = ld_ag(sl + 4); i2 = __double_as_longlong(ld_ag(sl + 5));
+        s3 = ld_ag(sl + 6); a3 = ld_ag(sl + 7); i3 = __double_as_longlong(ld_ag(sl + 8));
+      }
+      const int r1 = (int)(i1 >> 32), c1 = (int)i1;
+      const int w1 = wave_argmax_lane(s1, r1);
+      double bv = -1.0, ba = 0.0;
+      int br = INT_MAX, bc = 0;
+      if (w1 >= 0) {
+        bv = readlane_d(s1, w1); ba = readlane_d(a1, w1);
+        br = readlane_i(r1, w1); bc = readlane_i(c1, w1);
+      }
+      const SvdBest np_ = wave_svd_best(s2, (int)i2, a2), nq_ = wave_svd_best(s3, (int)i3, a3);
+      // rows p and q of the last rotation (p < q): ties to the smaller row
+      if (p >= 0) {
+        if (np_.v > bv || (np_.v == bv && p < br)) { bv = np_.v; ba = np_.a; br = p; bc = np_.c; }
+        if (nq_.v > bv || (nq_.v == bv && q < br)) { bv = nq_.v; ba = nq_.a; br = q; bc = nq_.c; }
+      }
+      if (lane == 0) {
+        s_ok = ok;
+        s_best[0] = bv; s_val[0] = ba; s_rc[0] = br; s_rc[1] = bc;
+        if (p >= k0 && p < k0 + nk) { best[p - k0] = np_.v; arg[p - k0] = np_.c; val[p - k0] = np_.a; }
+        if (q >= k0 && q < k0 + nk) { best[q - k0] = nq_.v; arg[q - k0] = nq_.c; val[q - k0] = nq_.a; }
+      }
+    }
+    __syncthreads();
+    if (!s_ok) { failed = true; break; }
+    vsel = s_best[0];
+    if (n < 2 || vsel <= d.thr) break;
+    if (rot >= d.maxrot) { status = ST_MAXROT; break; }
+    const double apq = s_val[0];
+    if (apq == 0.0) { status = ST_STALL; break; }
+    p = min(s_rc[0], s_rc[1]);
+    q = max(s_rc[0], s_rc[1]);
+    // ---- columns p, q: the loads first, the parameters overlap them
+    const bool ownp = p >= k0 && p < k0 + nk, ownq = q >= k0 && q < k0 + nk;
+    double* gp = Yc + (size_t)p * ldc;
+    double* gq = Yc + (size_t)q * ldc;
+    constexpr int kU = 4;
+    double t = 0.0, cs = 1.0, sn = 0.0;
+    for (int i0 = 0; i0 < m; i0 += kU * NT) {
+      double u[kU], w[kU];
+#pragma unroll
+      for (int e = 0; e < kU; ++e) {
+        const int i = min(i0 + e * NT + tid, m - 1);
+        u[e] = ld_ag(gp + i);
+        w[e] = ld_ag(gq + i);
+      }
+      if (i0 == 0) rot_params<double>(diag[p], diag[q], apq, t, cs, sn);
+#pragma unroll
+      for (int e = 0; e < kU; ++e) {
+        const int i = i0 + e * NT + tid;
+        if (i < m) {
+          const double np_ = cs * u[e] + sn * w[e], nq_ = cs * w[e] - sn * u[e];
+          colp[i] = np_;
+          colq[i] = nq_;
+          if (ownp) { Ys[(size_t)(p - k0) * S + i] = np_; }
+          if (ownq) { Ys[(size_t)(q - k0) * S + i] = nq_; }
+        }
+      }
+    }
+    if (tid == 0 && g == 0 && d.plog && rot < d.logcap) {
+      d.plog[2 * rot] = p;
+      d.plog[2 * rot + 1] = q;
+    }
+    ++rot;
+    __syncthreads();
+    // ---- dot products of this workgroup's columns with p (tasks 0 .. nk - 1) and q, and of p
+    // and q with themselves; the last wave rotates this workgroup's part of V^T and stores the
+    // columns that it owns
+    for (int task = tid; task < 2 * nk + 2; task += NT) {
+      const bool self = task >= 2 * nk;
+      const bool onp = self ? task == 2 * nk : task < nk;
+      const int k = onp ? task : task - nk;
+      const double* u = onp ? colp : colq;
+      const double x = dot_in_order(u, self ? u : Ys + (size_t)k * S, m);
+      if (self) s_new[onp ? 0 : 1] = x;
+      else (onp ? xp : xq)[k] = x;
+    }
+    if (wv == NW - 1) {
+      if (d.Vt) {
+        for (int i = k0 + lane; i < k0 + nk; i += 64) {
+          const double u = d.Vt[(size_t)p * ldv + i], w = d.Vt[(size_t)q * ldv + i];
+          d.Vt[(size_t)p * ldv + i] = cs * u + sn * w;
+          d.Vt[(size_t)q * ldv + i] = cs * w - sn * u;
+        }
+      }
+      if (ownp)
+        for (int i = lane; i < m; i += 64) st_ag(gp + i, colp[i]);
+      if (ownq)
+        for (int i = lane; i < m; i += 64) st_ag(gq + i, colq[i]);
+    }
+    __syncthreads();
+    // ---- entries of A, row caches (wave 0)
+    const double app = s_new[0], aqq = s_new[1];
+    if (wv == 0) {
+      vp = vq = -1.0;
+      ap = aq = 0.0;
+      cp = cq = INT_MAX;
+      for (int t0 = lane; t0 < nk; t0 += 64) {
+        const int k = k0 + t0;
+        const double x = xp[t0], y = xq[t0];
+        st_ag(d.G + (size_t)p * ldg + k, x);
+        st_ag(d.G + (size_t)k * ldg + p, x);
+        st_ag(d.G + (size_t)q * ldg + k, y);
+        st_ag(d.G + (size_t)k * ldg + q, y);
+        const double akk = k == p ? app : (k == q ? aqq : diag[k]);
+        const double sp = svd_score<PIV>(akk, app, x);
+        const double sq = svd_score<PIV>(akk, aqq, y);
+        if (k != p && sp > vp) { vp = sp; cp = k; ap = x; }
+        if (k != q && sq > vq) { vq = sq; cq = k; aq = y; }
+        if (k == p || k == q) continue;
+        double b = best[t0];
+        int ak = arg[t0];
+        if (ak == p || ak == q) {
+          double z = sp, zv = x;
+          int col = p;
+          if (sq > z) { z = sq; zv = y; col = q; }
+          if (z > b || (z == b && col <= ak)) {
+            best[t0] = z;
+            arg[t0] = col;
+            val[t0] = zv;
+          } else {
+            list[atomicAdd(&s_cnt, 1)] = t0;
+          }
+        } else {
+          double bvv = val[t0];
+          if (sp > b || (sp == b && p < ak)) { b = sp; ak = p; bvv = x; }
+          if (sq > b || (sq == b && q < ak)) { b = sq; ak = q; bvv = y; }
+          best[t0] = b;
+          arg[t0] = ak;
+          val[t0] = bvv;
+        }
+      }
+    }
+    __syncthreads();
+    const int cnt = s_cnt;
+    if (cnt > 0) {
+      // full rescans, one wave per row; the entries stored in this rotation from LDS
+      for (int e = wv; e < cnt; e += NW) {
+        const int t0 = list[e], k = k0 + t0;
+        const double akk = diag[k];
+        double bv = -1.0, bav = 0.0;
+        int bc = INT_MAX;
+        for (int l = lane; l < n; l += 64) {
+          if (l == k) continue;
+          const double gv = ld_ag(d.G + (size_t)k * ldg + l);
+          const double all = l == p ? app : (l == q ? aqq : diag[l]);
+          const double z = l == p ? xp[t0] : (l == q ? xq[t0] : gv);
+          const double x = svd_score<PIV>(akk, all, z);
+          if (x > bv) { bv = x; bc = l; bav = z; }
+        }
+        const SvdBest r = wave_svd_best(bv, bc, bav);
+        if (lane == 0) { best[t0] = r.v; arg[t0] = r.c; val[t0] = r.a; }
+      }
+      resc += cnt;
+      __syncthreads();
+    }
+    if (tid == 0) {
+      s_cnt = 0;
+      diag[p] = app;
+      diag[q] = aqq;
+    }
+  }
+  if (failed) return;  // the host reports a device error
+  __syncthreads();
+  for (int k = 0; k < nk; ++k)
+    for (int i = tid; i < m; i += NT) d.Y[(size_t)i * d.ldy + k0 + k] = Ys[(size_t)k * S + i];
+  if (tid == 0 && resc)
+    atomicAdd(reinterpret_cast<unsigned long long*>(&d.ctl->rescans), (unsigned long long)resc);
+  if (tid == 0 && g == 0) {
+    d.ctl->rotations = rot;
+    d.ctl->status = status;
+    d.ctl->done = 1;
+    d.ctl->final_sel = vsel;
+  }
+}
+
 // ------------------------------------------------------------------ output
 // rank[k] = position of column k in descending order of sigma_k = sqrt(a_kk) (stable);
 // S[rank[k]] = sigma_k.
@@ -714,6 +1073,60 @@ hipError_t launch_svd_jacobi(const SDesc& d, hipStream_t s) {
   if (d.pivot == 0) return svd_jacobi_t<0>(d, s);
   if (d.pivot == 1) return svd_jacobi_t<1>(d, s);
   return svd_jacobi_t<2>(d, s);
+}
+
+// Columns per workgroup and workgroups of the several-workgroup kernel; false where a slice
+// of B does not fit in LDS (the one-workgroup kernel then reads B from device memory) or the
+// one-workgroup resident kernel holds all of it.
+static bool svd_mw_shape(int m, int n, int* c, int* G) {
+  if (n < 2 || svd_resident(m, n)) return false;
+  *c = std::max(4, (n + kSvdMwGroups - 1) / kSvdMwGroups);
+  *G = (n + *c - 1) / *c;
+  return svd_mw_lds(m, n, *c) + 1024 <= (size_t)svd_max_lds();
+}
+
+static inline int svd_mw_ldc(int m) { return (m + 1) & ~1; }
+
+size_t svd_mw_bytes(int m, int n) {
+  int c, G;
+  if (!svd_mw_shape(m, n, &c, &G)) return 0;
+  return sizeof(MwCtl) + ((size_t)2 * G * kSvdMwWords + (size_t)n * svd_mw_ldc(m)) * 8;
+}
+
+template <int PIV>
+static hipError_t svd_mw_t(const SDesc& d, MwCtl* mc, int c, int G, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_rowbest<PIV>, dim3((d.n + 3) / 4), dim3(256), 0, s, d.G, d.ldg,
+                     d.n, d.best, d.arg, d.diag);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  double* xb = (double*)(mc + 1);
+  double* Yc = xb + (size_t)2 * G * kSvdMwWords;
+  const int ldc = svd_mw_ldc(d.m);
+  // Yc[k][i] = Y[i][k]
+  hipLaunchKernelGGL(k_svd_columns, dim3((d.m + 31) / 32, (d.n + 31) / 32), dim3(256), 0, s, d.Y,
+                     d.ldy, d.m, d.n, Yc, ldc);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t sh = svd_mw_lds(d.m, d.n, c);
+  auto fn = k_svd_mw<PIV>;
+  if (sh > 65536) {
+    e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fn, dim3(G * kMwStride), dim3(kSvdMwThreads), sh, s, d, mc, xb, Yc, ldc, G,
+                     c);
+  return hipGetLastError();
+}
+
+hipError_t launch_svd_mw(const SDesc& d, void* buf, hipStream_t s) {
+  int c, G;
+  if (d.n > kSvdMaxN || !svd_mw_shape(d.m, d.n, &c, &G)) return hipErrorInvalidValue;
+  MwCtl* mc = (MwCtl*)buf;
+  hipError_t e = launch_zero_words(mc, (int)(sizeof(MwCtl) / 4), s);
+  if (e != hipSuccess) return e;
+  if (d.pivot == 0) return svd_mw_t<0>(d, mc, c, G, s);
+  if (d.pivot == 1) return svd_mw_t<1>(d, mc, c, G, s);
+  return svd_mw_t<2>(d, mc, c, G, s);
 }
 
 hipError_t launch_svd_out(const double* Y, int ldy, int m, const double* G, int ldg,
