@@ -28,15 +28,18 @@ namespace je {
 // in FP64): one fused operation instead of a product and a sum in every rotated entry.
 #define FP32_CONTRACT _Pragma("clang fp contract(fast)")
 
-// Block geometry: PB rows per block, PM = 2 PB per subproblem, LDS rows padded by 4 floats
-// (16-byte aligned), NT threads per workgroup so that both phases of an inner round give
-// every thread four entries of S.
+// Block geometry: PB rows per block, PM = 2 PB per subproblem, NT threads per workgroup, LDS row
+// stride PL (16-byte aligned).  16-row blocks: 256 threads, one 2 x 2 block of S and one 16 x 16
+// matrix-core tile per thread and wave; their rows are 48 floats apart, so that four rows of 16
+// columns, what a wave reads at once, fall on 64 different banks.  32-row blocks: 512 threads,
+// two of each.
 template <int PB>
 struct Blk {
-  static_assert(PB % 4 == 0, "tiles move four consecutive floats per lane");
+  static_assert(PB == 16 || PB == 32, "block rows");
   static constexpr int PM = 2 * PB;
-  static constexpr int PL = PM + 4;
-  static constexpr int NT = PB * PM / 4;
+  static constexpr int PL = PB == 16 ? PM + 16 : PM + 4;
+  static constexpr int NT = 16 * PB;
+  static constexpr int TW = PM / 16 * (PM / 16) / (NT / 64);  // tiles of a PM x PM product per wave
 };
 
 // Index pair k of round r of the circle method on M indices (index M - 1 fixed).
@@ -172,104 +175,6 @@ __device__ __forceinline__ void inner_pair(int full, int r, int k, int& p, int& 
   }
 }
 
-// Two-phase inner round (the form used for 16-row blocks).  Both phases read rows only.  With J the product of the round's disjoint
-// rotations, the row phase forms M = J^T S and stores it transposed, W = M^T; the second
-// phase forms J^T W = (S J ... )^T, i.e. the rotated matrix J^T S J read by rows (it is
-// symmetric up to rounding; its upper triangle is the one used).  A lane keeps the same
-// pair and columns in both phases, so its c, s stay in registers.
-template <int PB>
-__device__ __forceinline__ void solve_body_rows(float (*S)[Blk<PB>::PL], float (*W)[Blk<PB>::PL],
-                                           float (*Ut)[Blk<PB>::PL], const float* Ain,
-                                           float* Aout, int np, int2 pr, float* __restrict__ Uo,
-                                           int inner_max, int full, float tol2, float rho2,
-                                           bool preloaded) {
-  FP32_CONTRACT
-  constexpr int PM = Blk<PB>::PM, NT = Blk<PB>::NT, LB = PM / 4;
-  __shared__ float red[2][NT / 64];
-  const int tid = threadIdx.x;
-  if (!preloaded) {
-    load_pair_block<PB>(S, Ain, np, pr, pr);
-    set_identity<PB>(Ut);
-    __syncthreads();
-  }
-  // pair kb, columns jb .. jb+3 (the LB lanes of a pair share one wave)
-  const int kb = tid / LB, jb = (tid % LB) * 4;
-  const int nr = full ? PM - 1 : PB;
-  float prev_off = 3.4e38f;
-  for (int sw = 0; sw < inner_max; ++sw) {
-    for (int r = 0; r < nr; ++r) {
-      int p, q;
-      inner_pair<PB>(full, r, kb, p, q);
-      // every lane of the pair reads the 2x2 block before any lane of it stores
-      float app = S[p][p], aqq = S[q][q];
-      const float apq = S[p][q];
-      const float4 x = *reinterpret_cast<const float4*>(&S[p][jb]);
-      const float4 y = *reinterpret_cast<const float4*>(&S[q][jb]);
-      // rows p, q of U^T belong to this pair's lanes alone in this round: rotated here,
-      // beside the first phase, off the second phase's dependency chain
-      const float4 up = *reinterpret_cast<const float4*>(&Ut[p][jb]);
-      const float4 uq = *reinterpret_cast<const float4*>(&Ut[q][jb]);
-      float c = 1.0f, s = 0.0f;
-      const bool skip = apq == 0.0f || f32_noise_pair(app, aqq, apq);
-      if (!skip) {
-        float t;
-        rot_fast(app, aqq, apq, t, c, s);
-        app = app + t * apq;
-        aqq = aqq - t * apq;
-      }
-      const float z = skip ? apq : 0.0f;
-      W[jb + 0][p] = c * x.x + s * y.x; W[jb + 0][q] = c * y.x - s * x.x;
-      W[jb + 1][p] = c * x.y + s * y.y; W[jb + 1][q] = c * y.y - s * x.y;
-      W[jb + 2][p] = c * x.z + s * y.z; W[jb + 2][q] = c * y.z - s * x.z;
-      W[jb + 3][p] = c * x.w + s * y.w; W[jb + 3][q] = c * y.w - s * x.w;
-      {
-        float4 po, qo;
-        po.x = c * up.x + s * uq.x; qo.x = c * uq.x - s * up.x;
-        po.y = c * up.y + s * uq.y; qo.y = c * uq.y - s * up.y;
-        po.z = c * up.z + s * uq.z; qo.z = c * uq.z - s * up.z;
-        po.w = c * up.w + s * uq.w; qo.w = c * uq.w - s * up.w;
-        *reinterpret_cast<float4*>(&Ut[p][jb]) = po;
-        *reinterpret_cast<float4*>(&Ut[q][jb]) = qo;
-      }
-      __syncthreads();
-      {
-        const float4 wx = *reinterpret_cast<const float4*>(&W[p][jb]);
-        const float4 wy = *reinterpret_cast<const float4*>(&W[q][jb]);
-        float xo[4] = {c * wx.x + s * wy.x, c * wx.y + s * wy.y, c * wx.z + s * wy.z,
-                       c * wx.w + s * wy.w};
-        float yo[4] = {c * wy.x - s * wx.x, c * wy.y - s * wx.y, c * wy.z - s * wx.z,
-                       c * wy.w - s * wx.w};
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if (jb + v == p) { xo[v] = app; yo[v] = z; }
-          if (jb + v == q) { xo[v] = z; yo[v] = aqq; }
-        }
-        *reinterpret_cast<float4*>(&S[p][jb]) = make_float4(xo[0], xo[1], xo[2], xo[3]);
-        *reinterpret_cast<float4*>(&S[q][jb]) = make_float4(yo[0], yo[1], yo[2], yo[3]);
-      }
-      __syncthreads();
-    }
-    if (sw + 1 < inner_max) {
-      // off(S) and ||S||_F decide whether another inner sweep pays
-      float so = 0.0f, sd = 0.0f;
-      for (int e = tid; e < PM * PM; e += NT) {
-        int i = e / PM, j = e % PM;
-        float v = S[i][j] * S[i][j];
-        if (i == j) sd += v; else so += v;
-      }
-      for (int o = 32; o > 0; o >>= 1) { so += __shfl_xor(so, o); sd += __shfl_xor(sd, o); }
-      if ((tid & 63) == 0) { red[0][tid >> 6] = so; red[1][tid >> 6] = sd; }
-      __syncthreads();
-      float off = 0.0f, dg = 0.0f;
-      for (int w = 0; w < NT / 64; ++w) { off += red[0][w]; dg += red[1][w]; }
-      __syncthreads();
-      if (off <= tol2 * (off + dg) || off >= rho2 * prev_off) break;
-      prev_off = off;
-    }
-  }
-  store_solved<PB>(S, Ut, Uo, Aout, np, pr);
-}
-
 // Rotation of one pair of an inner round, from the current subproblem: cosine, sine, the
 // new diagonal entries and the new pivot entry (0, or a_pq itself when the pair is
 // skipped, see f32_noise_pair).
@@ -289,6 +194,22 @@ __device__ __forceinline__ RotF pair_rot(const float (*S)[PL], int p, int q) {
     r.naqq = aqq - t * apq;
     r.z = 0.0f;
   }
+  return r;
+}
+
+// The same from the three entries without branches (the rotation is evaluated and dropped for a
+// skipped pair), so that two of them overlap.
+__device__ __forceinline__ RotF entry_rot(float app, float aqq, float apq) {
+  FP32_CONTRACT
+  float t, c, s;
+  rot_fast(app, aqq, apq, t, c, s);
+  const bool skip = apq == 0.0f || f32_noise_pair(app, aqq, apq);
+  RotF r;
+  r.c = skip ? 1.0f : c;
+  r.s = skip ? 0.0f : s;
+  r.napp = skip ? app : app + t * apq;
+  r.naqq = skip ? aqq : aqq - t * apq;
+  r.z = skip ? apq : 0.0f;
   return r;
 }
 
@@ -418,6 +339,88 @@ __device__ __forceinline__ void solve_body_blocks(float (*S)[Blk<PB>::PL], float
   store_solved<PB>(S, Ut, Uo, Aout, np, pr);
 }
 
+// The same in one 2 x 2 block per thread, for 16-row blocks (four waves, one to a SIMD): thread
+// (b, c) = (tid / 16, tid mod 16) holds the block of row pair b and column pair c and columns
+// 2 c, 2 c + 1 of rows p, q of U^T of pair b.  Latency bounds an inner round (few workgroups, a
+// chain of LDS reads, one rotation, LDS writes and a barrier), so every thread evaluates both
+// rotations itself from broadcast reads, without branches between them, and one barrier ends
+// the round.  With two waves and two phases (rows, then columns, a barrier after each) the FP32
+// stage took 18.5 ms at n = 1024, 7.8 at 512 and 2.75 at 203; now 16.1, 7.0 and 2.35.  What is
+// left of a round (16 us at n = 1024, 7.9 of them the 16 inner rounds) is 18 LDS accesses of each
+// wave per inner round.
+template <int PB>
+__device__ __forceinline__ void solve_body_quads(float (*S)[Blk<PB>::PL], float (*W)[Blk<PB>::PL],
+                                                 float (*Ut)[Blk<PB>::PL], const float* Ain,
+                                                 float* Aout, int np, int2 pr,
+                                                 float* __restrict__ Uo, int inner_max, int full,
+                                                 float tol2, float rho2, bool preloaded) {
+  FP32_CONTRACT
+  constexpr int PM = Blk<PB>::PM, NT = Blk<PB>::NT, PL = Blk<PB>::PL;
+  static_assert(PM == 32 && NT == 256, "16-row blocks: 16 pairs, one block per thread");
+  __shared__ float red[2][NT / 64];
+  const int tid = threadIdx.x;
+  if (!preloaded) {
+    load_pair_block<PB>(S, Ain, np, pr, pr);
+    set_identity<PB>(Ut);
+    __syncthreads();
+  }
+  const int b = tid >> 4, c = tid & 15;
+  const int nr = full ? PM - 1 : PB;
+  float(*Sc)[PL] = S;
+  float(*Sn)[PL] = W;
+  float prev_off = 3.4e38f;
+  for (int sw = 0; sw < inner_max; ++sw) {
+    for (int r = 0; r < nr; ++r) {
+      int pb, qb, pc, qc;
+      inner_pair<PB>(full, r, b, pb, qb);
+      inner_pair<PB>(full, r, c, pc, qc);
+      float x = Sc[pb][pc], y = Sc[pb][qc], z = Sc[qb][pc], w = Sc[qb][qc];
+      const float2 up = *reinterpret_cast<const float2*>(&Ut[pb][2 * c]);
+      const float2 uq = *reinterpret_cast<const float2*>(&Ut[qb][2 * c]);
+      const float bpp = Sc[pb][pb], bqq = Sc[qb][qb], bpq = Sc[pb][qb];
+      const float cpp = Sc[pc][pc], cqq = Sc[qc][qc], cpq = Sc[pc][qc];
+      const RotF rb = entry_rot(bpp, bqq, bpq);
+      const RotF rc = entry_rot(cpp, cqq, cpq);
+      rot_block(rb, rc, b == c, x, y, z, w);
+      Sn[pb][pc] = x; Sn[pb][qc] = y; Sn[qb][pc] = z; Sn[qb][qc] = w;
+      float2 po, qo;
+      po.x = rb.c * up.x + rb.s * uq.x; qo.x = rb.c * uq.x - rb.s * up.x;
+      po.y = rb.c * up.y + rb.s * uq.y; qo.y = rb.c * uq.y - rb.s * up.y;
+      *reinterpret_cast<float2*>(&Ut[pb][2 * c]) = po;
+      *reinterpret_cast<float2*>(&Ut[qb][2 * c]) = qo;
+      __syncthreads();
+      float(*t)[PL] = Sc;
+      Sc = Sn;
+      Sn = t;
+    }
+    if (sw + 1 < inner_max) {
+      // off(S) and ||S||_F decide whether another inner sweep pays
+      float so = 0.0f, sd = 0.0f;
+      for (int e = tid; e < PM * PM; e += NT) {
+        int i = e / PM, j = e % PM;
+        float v = Sc[i][j] * Sc[i][j];
+        if (i == j) sd += v; else so += v;
+      }
+      for (int o = 32; o > 0; o >>= 1) { so += __shfl_xor(so, o); sd += __shfl_xor(sd, o); }
+      if ((tid & 63) == 0) { red[0][tid >> 6] = so; red[1][tid >> 6] = sd; }
+      __syncthreads();
+      float off = 0.0f, dg = 0.0f;
+      for (int w = 0; w < NT / 64; ++w) { off += red[0][w]; dg += red[1][w]; }
+      __syncthreads();
+      if (off <= tol2 * (off + dg) || off >= rho2 * prev_off) break;
+      prev_off = off;
+    }
+  }
+  if (Sc != S) {  // the result ends in S (callers read it there)
+    for (int e = tid; e < PM * PM; e += NT) {
+      int i = e / PM, j = e % PM;
+      S[i][j] = Sc[i][j];
+    }
+    __syncthreads();
+  }
+  store_solved<PB>(S, Ut, Uo, Aout, np, pr);
+}
+
 template <int PB>
 __device__ __forceinline__ void solve_body(float (*S)[Blk<PB>::PL], float (*W)[Blk<PB>::PL],
                                            float (*Ut)[Blk<PB>::PL], const float* Ain,
@@ -425,28 +428,28 @@ __device__ __forceinline__ void solve_body(float (*S)[Blk<PB>::PL], float (*W)[B
                                            int inner_max, int full, float tol2, float rho2,
                                            bool preloaded = false) {
   if constexpr (PB == 16)
-    solve_body_rows<PB>(S, W, Ut, Ain, Aout, np, pr, Uo, inner_max, full, tol2, rho2, preloaded);
+    solve_body_quads<PB>(S, W, Ut, Ain, Aout, np, pr, Uo, inner_max, full, tol2, rho2,
+                         preloaded);
   else
     solve_body_blocks<PB>(S, W, Ut, Ain, Aout, np, pr, Uo, inner_max, full, tol2, rho2,
                           preloaded);
 }
 
 // out (PM x PM) = X^T Y if TA, else X Y; X, Y in LDS.  On the matrix cores
-// (v_mfma_f32_16x16x4f32): the output is split into 16 x 16 tiles, two per wave (wave w
-// owns tiles 2w and 2w + 1, row-major over the (PM/16)^2 tiles), K advances by 4 per
+// (v_mfma_f32_16x16x4f32): the output is split into 16 x 16 tiles, TW per wave (wave w
+// owns tiles TW w .. TW w + TW - 1, row-major over the (PM/16)^2 tiles), K advances by 4 per
 // instruction.  Operand layout: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k; result
 // D[i][j] in lane j + 16 (i / 4), register i % 4 (checked by an in-bounds probe).
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 template <int PB, bool TA>
 __device__ __forceinline__ void tile_mfma(float (*X)[Blk<PB>::PL], float (*Y)[Blk<PB>::PL],
-                                          f4 (&acc)[2]) {
-  constexpr int PM = Blk<PB>::PM, TT = PM / 16;
-  static_assert(Blk<PB>::NT / 64 * 2 == TT * TT, "two 16 x 16 tiles per wave");
-  const int l = threadIdx.x & 63, t0 = (threadIdx.x >> 6) * 2;
+                                          f4 (&acc)[Blk<PB>::TW]) {
+  constexpr int PM = Blk<PB>::PM, TT = PM / 16, TW = Blk<PB>::TW;
+  const int l = threadIdx.x & 63, t0 = (threadIdx.x >> 6) * TW;
   const int li = l & 15, lk = l >> 4;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
+  for (int u = 0; u < TW; ++u) {
     const int ti = (t0 + u) / TT, tj = (t0 + u) % TT;
     f4 c = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -463,15 +466,16 @@ __device__ __forceinline__ void tile_mfma(float (*X)[Blk<PB>::PL], float (*Y)[Bl
 template <int PB>
 __device__ __forceinline__ void tile_rc(int u, int v, int& i, int& j) {
   constexpr int TT = Blk<PB>::PM / 16;
-  const int l = threadIdx.x & 63, t = (threadIdx.x >> 6) * 2 + u;
+  const int l = threadIdx.x & 63, t = (threadIdx.x >> 6) * Blk<PB>::TW + u;
   i = 16 * (t / TT) + 4 * (l >> 4) + v;
   j = 16 * (t % TT) + (l & 15);
 }
 
 template <int PB>
-__device__ __forceinline__ void tile_store_lds(float (*T)[Blk<PB>::PL], const f4 (&acc)[2]) {
+__device__ __forceinline__ void tile_store_lds(float (*T)[Blk<PB>::PL],
+                                               const f4 (&acc)[Blk<PB>::TW]) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int u = 0; u < Blk<PB>::TW; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       int i, j;
@@ -504,14 +508,14 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_apply_a(float* __restrict
     Ab[i][j] = A[(size_t)blk_row<PB>(pp.x, pp.y, i) * np + blk_row<PB>(pr.x, pr.y, j)];
   }
   __syncthreads();
-  f4 acc[2];
+  f4 acc[Blk<PB>::TW];
   tile_mfma<PB, true>(Up, Ab, acc);  // T = U_P^T A_PR
   __syncthreads();
   tile_store_lds<PB>(Ab, acc);
   __syncthreads();
   tile_mfma<PB, false>(Ab, Ur, acc);  // T U_R
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int u = 0; u < Blk<PB>::TW; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       int i, j;
@@ -523,7 +527,7 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_apply_a(float* __restrict
 }
 
 // V <- V U_R on the columns of block pair R, for the tile of PM rows from r0 (RT threads,
-// two 16 x 16 output tiles per wave on the matrix cores).
+// 16 x 16 output tiles on the matrix cores).
 template <int PB, bool STAGED = false>
 __device__ __forceinline__ void vtile_body(float (*Ur)[Blk<PB>::PL], float (*Vb)[Blk<PB>::PL],
                                            float* __restrict__ V, int nrows, int np, int r0,
@@ -540,7 +544,7 @@ __device__ __forceinline__ void vtile_body(float (*Ur)[Blk<PB>::PL], float (*Vb)
                          : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
   __syncthreads();
-  f4 acc[2];
+  f4 acc[Blk<PB>::TW];
   tile_mfma<PB, false>(Vb, Ur, acc);
   if constexpr (STAGED) {
     // through LDS, so that rows are stored four consecutive columns per lane (measured
@@ -557,7 +561,7 @@ __device__ __forceinline__ void vtile_body(float (*Ur)[Blk<PB>::PL], float (*Vb)
     }
   } else {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < Blk<PB>::TW; ++u)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         int i, j;
@@ -628,7 +632,9 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_fused(
   const int ns = apply_only ? 0 : nb2, na = nb2 * (nb2 - 1) / 2;
   int b = blockIdx.x;
   if (b < ns) {
-    // ---- solve of round r, pair b = (I, J)
+    // ---- solve of round r, pair b = (I, J): the round's longest chain, so its waves go before
+    // those of the updates that share their SIMDs
+    __builtin_amdgcn_s_setprio(3);
     float(*S)[PL] = lds[0];
     float(*W)[PL] = lds[1];
     float(*Ut)[PL] = lds[2];
@@ -641,11 +647,15 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_fused(
     load_pair_block<PB>(W, Acur, np, PP, RR);
     load_factor<PB>(Ut, UR);
     __syncthreads();
-    // T = A_PR U_R(:, hJ): PM x PB, one 16 x 16 tile per wave
-    const f4 t = mfma_tile<PL, false>(W, 0, Ut, hJ * PB, PM, w / TB, w % TB);
+    // T = A_PR U_R(:, hJ): PM x PB, one 16 x 16 tile on each of the first 2 TB^2 waves
+    f4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (w < 2 * TB * TB) t = mfma_tile<PL, false>(W, 0, Ut, hJ * PB, PM, w / TB, w % TB);
     __syncthreads();
+    if (w < 2 * TB * TB) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) S[16 * (w / TB) + 4 * (l >> 4) + v][16 * (w % TB) + (l & 15)] = t[v];
+      for (int v = 0; v < 4; ++v)
+        S[16 * (w / TB) + 4 * (l >> 4) + v][16 * (w % TB) + (l & 15)] = t[v];
+    }
     load_factor<PB>(W, UP);
     __syncthreads();
     // X = U_P(:, hI)^T T: PB x PB, tiles on the first TB^2 waves
@@ -687,7 +697,7 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_fused(
     load_factor<PB>(Ur, Uprev + (size_t)R * PM * PM);
     load_pair_block<PB>(Ab, Acur, np, PP, RR);
     __syncthreads();
-    f4 acc[2];
+    f4 acc[Blk<PB>::TW];
     tile_mfma<PB, true>(Up, Ab, acc);
     __syncthreads();
     tile_store_lds<PB>(Ab, acc);
@@ -698,7 +708,7 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_block_fused(
     // consecutive columns per lane
     tile_store_lds<PB>(Up, acc);
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < Blk<PB>::TW; ++u)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         int i, j;
@@ -802,14 +812,15 @@ __global__ void k_gather_q(const float* __restrict__ V, int n, int ldv, double* 
   Q[(size_t)i * ldq + j] = (double)V[(size_t)i * ldv + j];
 }
 
-// Block rows of the FP32 stage.  32 when one 64 x 64 subproblem is the whole matrix
-// (n <= 64) and above n = 2048, where the per-round passes over A and V dominate and fewer
-// rounds pay; 16 in between, where the subproblem solves dominate and a 32 x 32 inner round
-// is cheaper (measured at n = 1024: 32.8 vs 36.4 ms; at n = 4096: 423 vs 297 ms).
+// Block rows of the FP32 stage.  16 up to n = 32, where one 32 x 32 subproblem is the whole
+// matrix (n = 32: 0.56 against 0.96 ms with 32 rows); 32 up to n = 64, where one 64 x 64 is (n =
+// 48: 0.92 against 1.11 ms with 16), and above n = 2048, where the per-round passes over A and V
+// dominate and fewer rounds pay (n = 3000: 71 against 108 ms); 16 in between, where the
+// subproblem solves dominate (n = 1024: 16.1 against 19.5 ms, n = 2048: 35.5 against 39.0).
 // `request` 16 or 32 overrides the choice (0: automatic).
 static int block_rows(int n, int request) {
   if (request == 16 || request == 32) return request;
-  return (n <= 64 || n > 2048) ? 32 : 16;
+  return ((n > 32 && n <= 64) || n > 2048) ? 32 : 16;
 }
 
 template <int PB>
@@ -1113,7 +1124,8 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_round_apply_a_b(
     BMat* __restrict__ mats, const int* __restrict__ act, const int* __restrict__ prefix,
     int count) {
   constexpr int PM = Blk<PB>::PM, PL = Blk<PB>::PL, NT = Blk<PB>::NT;
-  static_assert(2 * NT * 4 == PM * PM, "two four-float groups of a tile per thread");
+  // NG four-float groups of a tile per thread
+  constexpr int NG = PM * PM / 4 / NT;
   // two LDS tiles (four workgroups per CU): U_R waits in registers until U_P is consumed
   __shared__ __align__(16) float X[PM][PL], Y[PM][PL];
   const int L = xcd_order(blockIdx.x, gridDim.x);
@@ -1134,22 +1146,24 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_round_apply_a_b(
   const int np = bm.np, tid = threadIdx.x;
   // four consecutive columns per lane (they lie in one block: PB is a multiple of 4):
   // X = U_P, Y = A_PR, registers = U_R
-  const int i0 = tid / (PM / 4), j0 = (tid % (PM / 4)) * 4, i1 = i0 + NT / (PM / 4);
-  const float4 ur0 = *reinterpret_cast<const float4*>(Uh + i0 * PM + j0);
-  const float4 ur1 = *reinterpret_cast<const float4*>(Uh + i1 * PM + j0);
-  *reinterpret_cast<float4*>(&X[i0][j0]) = *reinterpret_cast<const float4*>(Ug + i0 * PM + j0);
-  *reinterpret_cast<float4*>(&X[i1][j0]) = *reinterpret_cast<const float4*>(Ug + i1 * PM + j0);
-  *reinterpret_cast<float4*>(&Y[i0][j0]) = *reinterpret_cast<const float4*>(
-      A + (size_t)blk_row<PB>(pp.x, pp.y, i0) * np + blk_row<PB>(pr.x, pr.y, j0));
-  *reinterpret_cast<float4*>(&Y[i1][j0]) = *reinterpret_cast<const float4*>(
-      A + (size_t)blk_row<PB>(pp.x, pp.y, i1) * np + blk_row<PB>(pr.x, pr.y, j0));
+  const int i0 = tid / (PM / 4), j0 = (tid % (PM / 4)) * 4;
+  float4 ur[NG];
+#pragma unroll
+  for (int u = 0; u < NG; ++u) {
+    const int i = i0 + u * (NT / (PM / 4));
+    ur[u] = *reinterpret_cast<const float4*>(Uh + i * PM + j0);
+    *reinterpret_cast<float4*>(&X[i][j0]) = *reinterpret_cast<const float4*>(Ug + i * PM + j0);
+    *reinterpret_cast<float4*>(&Y[i][j0]) = *reinterpret_cast<const float4*>(
+        A + (size_t)blk_row<PB>(pp.x, pp.y, i) * np + blk_row<PB>(pr.x, pr.y, j0));
+  }
   __syncthreads();
-  f4 acc[2];
+  f4 acc[Blk<PB>::TW];
   tile_mfma<PB, true>(X, Y, acc);  // T = U_P^T A_PR
   __syncthreads();
   tile_store_lds<PB>(Y, acc);
-  *reinterpret_cast<float4*>(&X[i0][j0]) = ur0;
-  *reinterpret_cast<float4*>(&X[i1][j0]) = ur1;
+#pragma unroll
+  for (int u = 0; u < NG; ++u)
+    *reinterpret_cast<float4*>(&X[i0 + u * (NT / (PM / 4))][j0]) = ur[u];
   __syncthreads();
   tile_mfma<PB, false>(Y, X, acc);  // T U_R
   __syncthreads();
@@ -1157,7 +1171,7 @@ __global__ __launch_bounds__(Blk<PB>::NT) void k_round_apply_a_b(
   // stored four consecutive columns per lane
   tile_store_lds<PB>(X, acc);
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int u = 0; u < Blk<PB>::TW; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       int i, j;
