@@ -131,7 +131,7 @@ typedef struct je_opts {
   int fp32_block;            /* rows per block of the FP32 stage: 0 by n (batches:  (0) */
                              /* 32), 16 or 32                                         */
   int jacobi_wgs;            /* FP64 phase of one problem: 0 automatic (several       */
-                             /* workgroups from n = 768), 1 one workgroup, 2 several */
+                             /* workgroups from n = 257), 1 one workgroup, 2 several */
                              /* workgroups when the matrix lives in HBM; same results */
                              /* (0); batches always use one workgroup per matrix      */
   int batch_threads;         /* batches: threads per workgroup of the persistent FP64  */

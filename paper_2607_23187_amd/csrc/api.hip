@@ -84,9 +84,11 @@ constexpr double kF32Tol2 = 0x1p-30;
 // Smallest n whose FP64 Jacobi phase runs on several workgroups by default, with one rotation
 // per exchange (MI355X, per rotation, one workgroup against several: n = 512 3.77 / 4.10 us,
 // 1024 5.02 / 4.29, 2048 7.23 / 4.77, 4096 11.52 / 5.37; the two cross near n = 670) and with
-// speculative rounds, where the scores of a round load one workgroup's SIMDs earlier (n = 400
-// 2.36 / 2.36 us, 512 2.57 / 2.36, 600 with a tight cluster 4.50 / 3.52, 1024 3.70 / 2.23).
-constexpr int kMultiWgMinN = 768, kMultiWgMinNSpec = 400;
+// speculative rounds, where one workgroup holds two rows per thread from n = 257 on (FP64 phase
+// of a mixed spectrum, one workgroup against several: n = 192 2.73 / 2.78 ms, 256 3.56 / 3.51,
+// 257 4.40 / 3.42, 400 8.35 / 5.88; of one tight cluster, with few rotations per round: n = 192
+// 16.8 / 20.5, 256 29.8 / 36.0, 288 44.9 / 43.5, 320 57.0 / 55.0).
+constexpr int kMultiWgMinN = 768, kMultiWgMinNSpec = 257;
 
 // Range of the entries solved as given: outside it the input is scaled by a power of two
 // (exact) so that squares in FP64 and the FP32 copy of the preconditioner stay in range.

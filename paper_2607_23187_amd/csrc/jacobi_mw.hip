@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64) void k_jacobi_mw(JDesc d, long long log_base, M
 // round costs two waits: one on the slots of candidates (publishing, store acknowledgements,
 // counter barrier, slot read), one on the vote.  The vote is a single 64-bit atomic per
 // workgroup, which carries the arrival and the first stage it could not prove: arrivals in
-// the low byte, six bits per stage above it (at most 32 workgroups each).
+// the low byte, seven bits per stage above it (at most 64 workgroups each).
 template <bool GAP_>
 struct MwExchange {
   static constexpr bool kExchange = true;
@@ -501,6 +501,386 @@ __global__ __launch_bounds__(64) void k_jacobi_spec_mw(JDesc d, long long log_ba
   spec_loop<RM, K, GAP>(d, log_base, ex);
 }
 
+// ------------------------------------------------------------------ speculative rounds, four
+// waves per workgroup
+// One row per lane (n <= 4096): the stages of a round are independent of each other up to the
+// proof (the entries of a row that an earlier stage rotates are formed from that rotation's
+// parameters), so the four waves of a workgroup hold the same 64 rows and take the stages j mod
+// 4 each: the loads, new entries, scores and stores of a round spread over the CU's four SIMDs.
+// Scores and entries meet in LDS; the selection, the proof and the caches, short and serial, are
+// repeated by every wave on its own copy.  The exchanges use flags instead of counters: a
+// workgroup stores its round number (with its vote) in a word of its own and all waves poll the
+// G words with one load, 0.1 us a try against 0.4 us for the round trip of an atomic.
+// The bound is the chain of short dependent steps of a round (about 2.9 rotations at n = 1024: per
+// rotation 0.55 us selection and loads, 0.24 entries and scores, 0.15 proof, 0.19 vote, 0.2 stores
+// and caches, 0.2 exchange).  Measured, FP64 phase per rotation, one wave per workgroup with
+// counters before and this now: mixed spectra n = 512 2.03 -> 1.58 us, 1024 2.20 -> 1.64, 2500
+// (nearly diagonal) 2.11 -> 1.77; tight cluster n = 600 4.06 -> 3.20.
+template <bool GAP>
+__global__ __launch_bounds__(256) void k_jacobi_spec4(JDesc d, long long log_base, MwCtl* mc,
+                                                      double* xb, int G) {
+  constexpr int K = 8, SW = 4;
+  if (blockIdx.x % kMwStride) return;
+  const int g = blockIdx.x / kMwStride;
+  if (g >= G) return;
+  extern __shared__ double s_diag[];
+  __shared__ double s_new[K][4][kWave];  // of stage j: scores p, q, new entries p, q
+  __shared__ int s_start;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = d.n, ld = d.ld;
+  const int k = g * kWave + lane, kc = min(k, n - 1);
+  double* A = d.A;
+  auto ld_a = [&](int r, int c) -> double { return ld_ag(A + (size_t)r * ld + c); };
+  auto st_a = [&](int r, int c, double v) { st_ag(A + (size_t)r * ld + c, v); };
+
+  if (wv == 0) {
+    const bool ok = mw_start(mc, G, g, 1);
+    if (lane == 0) s_start = ok;
+  }
+  for (int l = tid; l < n; l += 256) s_diag[l] = d.diag[l];
+  __syncthreads();
+  if (!s_start) return;
+
+  double dk = 0.0, bs = -1.0, bv = 0.0, bu = -1.0;
+  int ba = -1, bst = 0, tk = 0;
+  if (k < n) {
+    dk = d.diag[k]; bs = d.bs[k]; ba = d.ba[k]; bv = d.bv[k]; bst = d.bst[k];
+    bu = d.bu[k]; tk = d.ts[k];
+  }
+  long long rot = d.ctl->rotations, rescans = 0;
+  int status = ST_OK, done = 0, kmax = K, round = 1, votes = 0;
+  const double thr = d.thr;
+  double wsel = 0.0;
+  long long tph[6] = {0, 0, 0, 0, 0, 0}, tmark = 0;
+  const bool prof = d.prof != nullptr && g == 0 && wv == 0;
+  auto lap = [&](int i) {
+    if (prof) {
+      const long long t = (long long)wall_clock64();
+      tph[i] += t - tmark;
+      tmark = t;
+    }
+  };
+  // waits until every workgroup's word has reached `want` (in its high bits) and returns this
+  // lane's; -1 after a wait ran out
+  const int wi = min(lane, G - 1);
+  auto wait_all = [&](int* words, int want, int shift) -> int {
+    for (int outer = 0; outer < kMwSpinLimit / 64 && !ld_ag_i(&mc->abort); ++outer) {
+#pragma unroll 1
+      for (int spins = 0; spins < 64; ++spins) {
+        const int v = ld_ag_i(words + wi);
+        if (!__ballot((v >> shift) < want)) {
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          return v;
+        }
+      }
+    }
+    if (lane == 0) st_ag_i(&mc->abort, 1);
+    return -1;
+  };
+  auto uni = [](int v) -> int { return __builtin_amdgcn_readfirstlane(v); };
+  // every store of this workgroup's waves is in L2, then its flag is raised
+  auto arrive = [&]() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) st_word(&mc->flag[g], round);
+  };
+
+  for (;;) {
+    if (prof) tmark = (long long)wall_clock64();
+    // ---- publish the best candidate of every 16 lanes
+    ++round;
+    double* slots = xb + (size_t)(round & 1) * kMwMaxGroups * 16;
+    if (wv == 0) {
+      const int rc0 = k | (ba & 0x1fff) << 13 | bst << 26;
+      const double s0 = bs >= 0.0 ? bs : -1.0 - lane;
+      if (row_best(s0, scand_key(rc0))) {
+        double* p = slots + 4 * (4 * g + (lane >> 4));
+        st_ag(p, s0);
+        st_ag(p + 1, bv);
+        st_ag(p + 2, __longlong_as_double((long long)rc0));
+      }
+    }
+    lap(0);
+    arrive();
+    if (wait_all(mc->flag, round, 0) < 0) return;
+    lap(1);
+    // ---- the best of this lane's share of the candidates
+    SCand y = empty_scand();
+    {
+      SCand z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        z[u] = empty_scand();
+        if (u * 16 < G && lane + 64 * u < 4 * G) {
+          const double* p = slots + 4 * (lane + 64 * u);
+          z[u].s = ld_ag(p);
+          z[u].a = ld_ag(p + 1);
+          z[u].rc = (int)__double_as_longlong(ld_ag(p + 2));
+        }
+      }
+      int yk = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int zk = scand_key(z[u].rc);
+        if (z[u].s >= 0.0 && better(z[u].s, zk, y.s, yk)) { y = z[u]; yk = zk; }
+      }
+    }
+    // scores rounded to 17 bits, then the lane: this order picks the candidates below, and the
+    // first one where no other rounds to the same value
+    int order = y.s >= 0.0 ? (key32(y.s) & ~63) | (lane ^ 63) : -1;
+    int w;
+    {
+      const int top = uni(wave_max_i(order));
+      const unsigned long long same = __ballot((order | 63) == (top | 63));
+      w = top < 0 ? -1 : (top & 63) ^ 63;
+      if (top >= 0 && (same & (same - 1))) w = uni(wave_argmax_lane(y.s, scand_key(y.rc)));
+    }
+    wsel = w >= 0 ? readlane_d(y.s, w) : 0.0;  // no pair left: every entry is 0
+    if (n < 2) { done = 1; break; }
+    int rc = w >= 0 ? readlane_i(y.rc, w) : 0;
+    // ---- the winner must be exact
+    if (w >= 0 && scand_stale(rc)) {
+      const int r = scand_row(rc);
+      Cand c = empty_cand();
+      const double v = ld_a(r, kc);
+      if (k < n && k != r) cand_top2(c, sel_score<GAP>(s_diag[r], dk, v), k, v);
+      Cand e1 = empty_cand(), e2 = empty_cand();
+      wave_best3(e1, 0, c, c.c, e2, 0);
+      ++round;
+      double* bests = xb + 2 * kMwMaxGroups * 16 + (size_t)(round & 1) * kMwMaxGroups * 4;
+      if (tid == 0) put_cand(bests + 4 * g, c);
+      arrive();
+      if (wait_all(mc->flag, round, 0) < 0) return;
+      c = lane < G ? get_cand(bests + 4 * lane) : empty_cand();
+      e1 = empty_cand();
+      e2 = empty_cand();
+      wave_best3(e1, 0, c, c.c, e2, 0);
+      if (k == r) { bs = c.s; ba = c.c; bv = c.a; bu = c.u; bst = 0; }
+      ++rescans;
+      lap(3);
+      continue;
+    }
+    // ---- stop rules (checked before every rotation)
+    if (wsel <= thr) { done = 1; break; }
+    if (rot >= d.maxrot) { status = ST_MAXROT; done = 1; break; }
+    // (a score above thr >= 0 has a nonzero entry: no stall)
+    if (rot - log_base >= d.log_cap) break;  // log full: drain and resume
+    const long long room = min(d.maxrot - rot, d.log_cap - (rot - log_base));
+    const int klim = uni((int)min((long long)kmax, room));
+
+    // ---- candidates on rows and columns of their own: rotation j in lane j, as its lane here
+    // (my, pk: the round's rotation of this row and its other row; hs: the one that moves its
+    // best entry)
+    int vpq = 0, vw = w, my = -1, pk = kc, hs = K, kk = 0;
+    {
+      const int r1 = scand_row(y.rc), c1 = scand_stale(y.rc) ? r1 : scand_col(y.rc);
+      for (;;) {
+        const int x0 = scand_row(rc), x1 = scand_col(rc), p = min(x0, x1), q = max(x0, x1);
+        const bool here = lane == kk;
+        vpq = here ? p | q << 13 : vpq;
+        vw = here ? w : vw;
+        const bool piv = (k == p) | (k == q);
+        my = piv ? kk : my;
+        pk = piv ? p + q - k : pk;
+        hs = (!bst & ((ba == p) | (ba == q))) ? kk : hs;
+        ++kk;
+        if (kk >= klim) break;
+        const bool out = (r1 == p) | (r1 == q) | (c1 == p) | (c1 == q);
+        order = out ? -1 : order;
+        const int top = uni(wave_max_i(order));
+        if (top < 0) break;
+        w = (top & 63) ^ 63;
+        rc = readlane_i(y.rc, w);
+        if (scand_stale(rc)) break;
+      }
+    }
+    // the list ends where its scores do not decrease or reach the threshold
+    const double vs = __shfl(y.s, vw), va = __shfl(y.a, vw);
+    {
+      const double vprev = __shfl_up(vs, 1);
+      const unsigned long long cut = __ballot(lane > 0 && lane < kk && !(vs < vprev && vs > thr));
+      if (cut) kk = uni((int)__ffsll((long long)cut) - 1);
+      if (my >= kk) { my = -1; pk = kc; }
+    }
+    // ---- loads of this wave's stages, then the rotation parameters in lanes
+    double xv[2], yv[2], px[2] = {0.0, 0.0}, py[2] = {0.0, 0.0};
+    int pj[2], qj[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = wv + SW * u, pq = readlane_i(vpq, j);
+      pj[u] = pq & 0x1fff;
+      qj[u] = pq >> 13;
+      xv[u] = yv[u] = 0.0;
+      if (j < kk) {
+        xv[u] = ld_a(pj[u], kc);
+        yv[u] = ld_a(qj[u], kc);
+        if (__ballot(my >= 0 && my < j)) {
+          px[u] = ld_a(pj[u], pk);
+          py[u] = ld_a(qj[u], pk);
+        }
+      }
+    }
+    lap(2);
+    const double app = s_diag[vpq & 0x1fff], aqq = s_diag[vpq >> 13];
+    double vt, vc, vsn;
+    rot_params<double>(app, aqq, lane < kk ? va : 1.0, vt, vc, vsn);
+    const double vnp = app + vt * va, vnq = aqq - vt * va;
+    // this row's own rotation, for the stages after it
+    double mc_ = 1.0, ms_ = 0.0, dn = dk;
+    if (__ballot(my >= 0)) {
+      const int src = max(my, 0);
+      const double c0 = __shfl(vc, src), s0 = __shfl(vsn, src);
+      const double np0 = __shfl(vnp, src), nq0 = __shfl(vnq, src);
+      const bool isp = k < pk;
+      if (my >= 0) {
+        mc_ = c0;
+        ms_ = isp ? s0 : -s0;
+        dn = isp ? np0 : nq0;
+      }
+    }
+    // ---- new entries and scores of this wave's stages
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = wv + SW * u;
+      if (j < kk) {
+        const double c = readlane_d(vc, j), s = readlane_d(vsn, j);
+        const double np_ = readlane_d(vnp, j), nq_ = readlane_d(vnq, j);
+        const bool comp = my >= 0 && my < j;
+        const double xo = comp ? mc_ * xv[u] + ms_ * px[u] : xv[u];
+        const double yo = comp ? mc_ * yv[u] + ms_ * py[u] : yv[u];
+        const double dc = comp ? dn : dk;
+        xv[u] = c * xo + s * yo;
+        yv[u] = c * yo - s * xo;
+        s_new[j][0][lane] = sel_score<GAP>(dc, np_, xv[u]);
+        s_new[j][1][lane] = sel_score<GAP>(dc, nq_, yv[u]);
+        s_new[j][2][lane] = xv[u];
+        s_new[j][3][lane] = yv[u];
+      }
+    }
+    __syncthreads();
+    lap(4);
+    // ---- F = rotations proven (every wave on its own copy)
+    double sp[K], sq[K];
+    auto proven = [&](int j0, double& e, double& ob) -> int {  // of stages j0 .. j0 + 3
+      unsigned long long bad[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        sp[j0 + u] = s_new[j0 + u][0][lane];
+        sq[j0 + u] = s_new[j0 + u][1][lane];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + u;
+        const double next = readlane_d(vs, j + 1);
+        const bool piv = my == j;
+        e = (piv | (k >= n)) ? -1.0 : fmax(e, fmax(sp[j], sq[j]));
+        ob = piv ? -1.0 : (hs == j ? fmin(ob, bu) : ob);
+        bad[u] = __ballot(!(fmax(e, ob) < next));
+      }
+      int f = kk;
+#pragma unroll
+      for (int u = 3; u >= 0; --u)
+        if (j0 + u + 1 < kk && bad[u]) f = j0 + u + 1;
+      return f;
+    };
+    int F;
+    {
+      double e = -1.0;
+      double ob = (my >= 0 && !bst && ba == pk) ? bu : bs;
+      F = proven(0, e, ob);
+      if (F > 4) F = proven(4, e, ob);
+    }
+    // ---- vote: the loads of this workgroup are complete (their values are in LDS), so the
+    // stores that follow the vote elsewhere cannot meet them
+    if (kk > 1) {
+      ++votes;
+      if (tid == 0) st_word(&mc->ballot[g], votes << 4 | F);
+      const int v = wait_all(mc->ballot, votes, 4);
+      if (v < 0) return;
+      F = uni(-wave_max_i(-(v & 15)));
+    }
+    // ---- commit rotations 0 .. F - 1: the stores by the waves of their stages
+    const bool moved = my >= 0 && my < F;  // this row's partner rows store what precedes it
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = wv + SW * u, p = pj[u], q = qj[u];
+      if (j < F && k < n) {
+        if (k == p) st_a(q, p, 0.0);
+        else if (k == q) st_a(p, q, 0.0);
+        else if (!(moved && my > j)) {
+          st_a(p, k, xv[u]);
+          st_a(q, k, yv[u]);
+          st_a(k, p, xv[u]);
+          st_a(k, q, yv[u]);
+        }
+      }
+    }
+    if (wv == 0 && lane < F) {
+      const int p = vpq & 0x1fff, q = vpq >> 13;
+      s_diag[p] = vnp;
+      s_diag[q] = vnq;
+      if (g == 0) d.log[rot - log_base + lane] = RotEntry{p, q, vc, vsn};
+    }
+    RowNew rn{-1.0, -1.0, 0};
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      if (j < F) {
+        const bool in = !(moved & (my >= j));
+        row_insert(rn, in ? sp[j] : -1.0, 2 * j);
+        row_insert(rn, in ? sq[j] : -1.0, 2 * j + 1);
+      }
+    }
+    if (__ballot(rn.m1 > 0.0 && rn.m1 == rn.m2)) {
+      // equal best scores in a row: the smallest column
+      int col = 0x7fffffff;
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        if (j < F) {
+          const int pq = readlane_i(vpq, j);
+          const bool in = !(moved & (my >= j));
+          if (in && sp[j] == rn.m1 && (pq & 0x1fff) < col) { col = pq & 0x1fff; rn.code = 2 * j; }
+          if (in && sq[j] == rn.m1 && (pq >> 13) < col) { col = pq >> 13; rn.code = 2 * j + 1; }
+        }
+      }
+    }
+    {
+      const int pq = __shfl(vpq, rn.code >> 1);
+      const double a = s_new[rn.code >> 1][2 + (rn.code & 1)][lane];
+      if (k < n) {
+        if (moved) {
+          dk = dn;
+          tk = (int)(rot + my + 1);
+        }
+        const bool up = row_refresh(bs, ba, bu, bst, moved, hs < F, rn,
+                                    rn.code & 1 ? pq >> 13 : pq & 0x1fff);
+        bv = up ? a : bv;
+      }
+    }
+    rot += F;
+    kmax = min(K, F + 1 + (F == kk ? 1 : 0));
+    lap(5);
+  }
+
+  // ---- write the state back (a later launch may resume from it)
+  if (wv == 0 && k < n) {
+    d.diag[k] = dk; d.bs[k] = bs; d.ba[k] = ba; d.bv[k] = bv; d.bst[k] = bst;
+    d.bu[k] = bu; d.ts[k] = tk;
+  }
+  if (prof && lane == 0)
+    for (int i = 0; i < 6; ++i) d.prof[i] += tph[i];
+  if (g == 0 && tid == 0) {
+    JCtl* ctl = d.ctl;
+    ctl->rotations = rot;
+    ctl->rescans += rescans;
+    ctl->status = status;
+    ctl->done = done;
+    ctl->final_sel = wsel;
+    ctl->final_cert = GAP ? wsel : -1.0;
+    ctl->final_off = 0.0;
+  }
+}
+
 // Workgroups and rows per thread for n: G = ceil(n / 64) one-wave workgroups, at most 32 (one
 // per CU of an XCD) for one rotation per exchange and 64 for speculative rounds, where the
 // scores of a round bound the wave; RM rows per thread (1, 2 or 4).
@@ -514,11 +894,11 @@ void mw_shape(int n, bool spec, int* G, int* RM) {
 }
 
 size_t mw_bytes(int n) {
-  int G, RM, Gs;
+  int G, RM;
   mw_shape(n, false, &G, &RM);
-  mw_shape(n, true, &Gs, &RM);
   const size_t one = (size_t)2 * G * kMwWords;  // one rotation per exchange
-  const size_t spec = MwExchange<true>::kSlotWords + (size_t)2 * Gs * 4;
+  // (2 x 4 candidates of four words a workgroup and two rows' bests of four: both forms)
+  const size_t spec = 2 * kMwMaxGroups * 16 + (size_t)2 * kMwMaxGroups * 4;
   return sizeof(MwCtl) + std::max(one, spec) * sizeof(double);
 }
 
@@ -529,8 +909,15 @@ static hipError_t launch_mw_t(const JDesc& d, long long log_base, int G, MwCtl* 
                               hipStream_t s) {
   const size_t sh = (size_t)d.n * sizeof(double);
   auto fn = k_jacobi_mw<RM, GAP>;
-  if constexpr (RM <= 2)
-    if (jacobi_speculates(d.pivot, d.stop)) fn = k_jacobi_spec_mw<RM, RM == 1 ? 8 : 4, GAP>;
+  int threads = kWave;
+  if (jacobi_speculates(d.pivot, d.stop)) {
+    if constexpr (RM == 1) {
+      fn = k_jacobi_spec4<GAP>;
+      threads = 4 * kWave;
+    } else if constexpr (RM == 2) {
+      fn = k_jacobi_spec_mw<2, 4, GAP>;
+    }
+  }
   if (sh > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)fn,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
@@ -538,7 +925,7 @@ static hipError_t launch_mw_t(const JDesc& d, long long log_base, int G, MwCtl* 
   }
   hipError_t e = launch_zero_words(mc, (int)(sizeof(MwCtl) / 4), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fn, dim3(G * kMwStride), dim3(kWave), sh, s, d, log_base, mc, xb, G);
+  hipLaunchKernelGGL(fn, dim3(G * kMwStride), dim3(threads), sh, s, d, log_base, mc, xb, G);
   return hipGetLastError();
 }
 

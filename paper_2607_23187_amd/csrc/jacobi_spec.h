@@ -69,6 +69,36 @@ __device__ __forceinline__ bool row_best(double s, int key) {
   return win;
 }
 
+// A row's cache after a round.  The round's new entries of the row are inserted one by one into a
+// running best and second best, and the cache is refreshed once from those: the outcome is a
+// fresh cache (its exact best, a bound of the others) or a stale one (a bound of all), as one
+// refresh per rotation would leave, in a third of the instructions.
+struct RowNew {
+  double m1, m2;  // best and second best new score
+  int code;       // of the best: 2 * rotation + (1 for the entry in column q)
+};
+
+__device__ __forceinline__ void row_insert(RowNew& x, double v, int code) {
+  x.code = v > x.m1 ? code : x.code;
+  x.m2 = fmax(x.m2, fmin(x.m1, v));
+  x.m1 = fmax(x.m1, v);
+}
+
+// empty: the row was rotated in the round (x holds what followed); hit: its best entry's column
+// was.  True when the best new entry (column col) is the row's best now.
+__device__ __forceinline__ bool row_refresh(double& bs, int& ba, double& bu, int& bst, bool empty,
+                                            bool hit, const RowNew& x, int col) {
+  const double bound = empty ? -1.0 : (bst ? bs : bu);
+  const bool nobest = empty | (bst != 0) | hit;
+  const bool up = nobest ? x.m1 > bound : better(x.m1, col, bs, ba);
+  const double under = up ? fmax(x.m2, nobest ? -1.0 : bs) : (nobest ? -1.0 : x.m1);
+  bs = up ? x.m1 : (nobest ? bound : bs);
+  bu = fmax(bound, under);
+  ba = up ? col : (empty ? -1 : ba);
+  bst = (nobest & !up & (bound >= 0.0)) ? 1 : 0;
+  return up;
+}
+
 // The loop over one matrix.  Ex gives the exchange and the storage of A:
 //   T, GT        this thread owns rows k = T + i GT, i < RM (k < n)
 //   kExchange    false: one wave, which selects among its lanes' own candidates
@@ -184,9 +214,10 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
     // ---- candidates on rows and columns of their own, in descending order; the loads of
     // each one's rows are issued before the next is selected
     double xv[K][RM], yv[K][RM], px[K][RM], py[K][RM];
-    int my[RM], pk[RM];  // pivot this row belongs to and its other row
+    // the round's rotation of this row and its other row; the one that moves its best entry
+    int my[RM], pk[RM], hs[RM];
 #pragma unroll
-    for (int i = 0; i < RM; ++i) { my[i] = -1; pk[i] = min(ex.T + i * ex.GT, n - 1); }
+    for (int i = 0; i < RM; ++i) { my[i] = -1; pk[i] = min(ex.T + i * ex.GT, n - 1); hs[i] = K; }
     // rotation j in lane j: packed (p, q), score, entry
     int vpq = 0;
     double vs = 0.0, va = 0.0;
@@ -229,6 +260,7 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
             }
             my[i] = piv ? j : my[i];
             pk[i] = piv ? p + q - k : pk[i];
+            hs[i] = (!bst[i] & ((ba[i] == p) | (ba[i] == q))) ? j : hs[i];
           }
           // candidates sharing a row or column with this one are out
           const int r1 = scand_row(y.rc), c1 = scand_col(y.rc);
@@ -266,8 +298,6 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
 #pragma unroll
       for (int u = 0; u < kGroup; ++u) {
         const int j = j0 + u;
-        const int pq = readlane_i(vpq, j);
-        const int p = pq & 0x1fff, q = pq >> 13;
         const double c = readlane_d(vc, j), s = readlane_d(vsn, j);
         const double np_ = readlane_d(vnp, j), nq_ = readlane_d(vnq, j);
         const double next = readlane_d(vs, j + 1);
@@ -275,7 +305,7 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
           const int k = ex.T + i * ex.GT;
-          const bool piv = k == p || k == q;
+          const bool piv = my[i] == j, isp = k < pk[i];
           double xo = xv[j][i], yo = yv[j][i];
           if (j > 0) {
             // the entries as an earlier rotation of this row left them
@@ -293,11 +323,10 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
           sq[j][i] = sel_score<GAP>(dc[i], nq_, yn);
           const double ej = fmax(e[i], fmax(sp[j][i], sq[j][i]));
           e[i] = (piv || k >= n) ? -1.0 : ej;
-          const bool hit = !bst[i] && (ba[i] == p || ba[i] == q);
-          ob[i] = piv ? -1.0 : (hit ? fmin(ob[i], bu[i]) : ob[i]);
+          ob[i] = piv ? -1.0 : (hs[i] == j ? fmin(ob[i], bu[i]) : ob[i]);
           mc[i] = piv ? c : mc[i];
-          ms[i] = piv ? (k == p ? s : -s) : ms[i];
-          dc[i] = piv ? (k == p ? np_ : nq_) : dc[i];
+          ms[i] = piv ? (isp ? s : -s) : ms[i];
+          dc[i] = piv ? (isp ? np_ : nq_) : dc[i];
           over |= !(fmax(e[i], ob[i]) < next);
         }
         bad[u] = __ballot(over);
@@ -311,32 +340,78 @@ __device__ __forceinline__ bool spec_loop(const JDesc& d, long long log_base, Ex
     if (!ex.ok()) return false;
 
     // ---- commit rotations 0 .. F - 1
+    RowNew rn[RM];
+    double av[RM];  // the best new entry
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {
+      rn[i] = RowNew{-1.0, -1.0, 0};
+      av[i] = 0.0;
+    }
+    bool tie = false;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       if (j < F) {
         const int pq = readlane_i(vpq, j);
         const int p = pq & 0x1fff, q = pq >> 13;
-        const double np_ = readlane_d(vnp, j), nq_ = readlane_d(vnq, j);
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
           const int k = ex.T + i * ex.GT;
-          if (k >= n) continue;
-          if (k == p || k == q) {
-            const int o = k == p ? q : p;
-            ex.st(o, k, 0.0);
-            dk[i] = k == p ? np_ : nq_;
-            tk[i] = (int)(rot + j + 1);
-            bs[i] = -1.0; bv[i] = 0.0; bu[i] = -1.0; ba[i] = -1; bst[i] = 0;
-          } else if (!(my[i] > j && my[i] < F)) {
+          if (k < n) {
             // (a row rotated later in the round: its partner rows store the final entries)
+            const bool later = my[i] > j && my[i] < F;
             const double xn = xv[j][i], yn = yv[j][i];
-            ex.st(p, k, xn);
-            ex.st(q, k, yn);
-            ex.stm(k, p, xn);
-            ex.stm(k, q, yn);
-            refresh_entry(bs[i], ba[i], bv[i], bu[i], bst[i], p, q, sp[j][i], xn, sq[j][i], yn);
+            if (my[i] == j) {
+              ex.st(k == p ? q : p, k, 0.0);
+            } else if (!later) {
+              ex.st(p, k, xn);
+              ex.st(q, k, yn);
+              ex.stm(k, p, xn);
+              ex.stm(k, q, yn);
+            }
+            const bool in = my[i] != j && !later;
+            const double a = in ? sp[j][i] : -1.0, b = in ? sq[j][i] : -1.0;
+            av[i] = a > rn[i].m1 ? xn : av[i];
+            row_insert(rn[i], a, 2 * j);
+            av[i] = b > rn[i].m1 ? yn : av[i];
+            row_insert(rn[i], b, 2 * j + 1);
           }
         }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < RM; ++i) tie |= rn[i].m1 > 0.0 && rn[i].m1 == rn[i].m2;
+    if (__ballot(tie)) {
+      // equal best scores in a row: the smallest column
+#pragma unroll
+      for (int i = 0; i < RM; ++i) {
+        int col = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          if (j < F) {
+            const int pq = readlane_i(vpq, j);
+            const bool in = my[i] != j && !(my[i] > j && my[i] < F);
+            if (in && sp[j][i] == rn[i].m1 && (pq & 0x1fff) < col) {
+              col = pq & 0x1fff; rn[i].code = 2 * j; av[i] = xv[j][i];
+            }
+            if (in && sq[j][i] == rn[i].m1 && (pq >> 13) < col) {
+              col = pq >> 13; rn[i].code = 2 * j + 1; av[i] = yv[j][i];
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {
+      const int pq = __shfl(vpq, rn[i].code >> 1);
+      const int col = rn[i].code & 1 ? pq >> 13 : pq & 0x1fff;
+      const bool moved = my[i] >= 0 && my[i] < F;
+      if (ex.T + i * ex.GT < n) {
+        if (moved) {
+          dk[i] = dc[i];
+          tk[i] = (int)(rot + my[i] + 1);
+        }
+        const bool up = row_refresh(bs[i], ba[i], bu[i], bst[i], moved, hs[i] < F, rn[i], col);
+        bv[i] = up ? av[i] : bv[i];
       }
     }
     if (lane < F) {

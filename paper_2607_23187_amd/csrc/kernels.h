@@ -86,6 +86,8 @@ struct alignas(8) MwCtl {
   int pad;
   int xcc[kMwMaxGroups];      // XCC id of every workgroup
   unsigned long long vote[4]; // votes of the speculative rounds, used in turn
+  int flag[kMwMaxGroups];     // the four-wave kernel's rounds, and
+  int ballot[kMwMaxGroups];   // its votes (number << 4 | rotations proven), a word a workgroup
 };
 void mw_shape(int n, bool spec, int* G, int* RM);
 size_t mw_bytes(int n);

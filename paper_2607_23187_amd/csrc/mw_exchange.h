@@ -39,6 +39,11 @@ __device__ __forceinline__ void st_ag_i(int* p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same for a word: a flag behind stores that have been acknowledged.
+__device__ __forceinline__ void st_word(int* p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Arrival of this workgroup at exchange round `round` (1-based) and the wait for all G.
 // False when the wait ran out or another workgroup gave up (the abort flag is then set).
 __device__ __forceinline__ bool mw_sync(MwCtl* mc, int G, int round) {
