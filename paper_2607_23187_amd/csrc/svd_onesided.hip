@@ -633,7 +633,7 @@ __global__ __launch_bounds__(NT) void k_svd1(const SDesc d) {
 //   exchanges its best row and those two, after which all hold the same winner.
 // Bound: the dot products (dot_in_order), then the exchange (0.6 us) and the L2 reads of the
 // columns and of the rows rescanned.  One workgroup alone read all of B from L2 at 22 GB/s per
-// rotation: 1024 x 512 186 -> 17 us per rotation, 300 x 260 38.8 -> 9.5, 130 x 129 13.4 -> 6.6.
+// rotation: 1024 x 512 186 -> 14.6 us per rotation, 300 x 260 38.8 -> 9, 130 x 129 13.4 -> 6.6.
 constexpr int kSvdMwThreads = 256;
 constexpr int kSvdMwWords = 9;  // three candidates: score, entry, row << 32 | column
 
@@ -644,44 +644,38 @@ __host__ __device__ __forceinline__ size_t svd_mw_lds(int m, int n, int c) {
   return 8 * ((size_t)(c + 2) * svd_mw_stride(m) + n + 4 * (size_t)c) + 8 * (size_t)c;
 }
 
-// sum_i u_i y_i in index order, 16 elements in flight ahead of the sums.  What bounds it is the
-// LDS return path of the one wave (both factors, 16 bytes a lane in 21 cycles; the chain of
-// additions alone takes 8 cycles a step); handing u round a row of lanes on the DPP network
-// instead of reading it measured slower (1009 x 33: 18.7 against 17.2 us per rotation).
+// sum_i u_i y_i in index order, the operands of 8 terms in flight ahead of the sums.  What bounds
+// it is the LDS return path of the one wave (both factors, 16 bytes a lane in 21 cycles; the
+// chain of products and sums alone takes 10 cycles a step).  Two blocks in turn, each loaded while
+// the other is summed, measured 14.6 us per rotation at 1024 x 512; one block of 16 whose
+// operands and products move up by copies 16.9; handing u round a row of lanes on the DPP
+// network instead of reading it is slower again (1009 x 33: 18.7 against 17.2).
 __device__ __forceinline__ double dot_in_order(const double* u, const double* y, int m) {
-  constexpr int kB = 16;
+  constexpr int kB = 8;
   double x = 0.0;
   int i = 0;
   if (m >= 2 * kB) {
-    double pr[kB];
-    double2 a[kB / 2], b[kB / 2];
+    double2 a[kB / 2], b[kB / 2], v[kB / 2], w[kB / 2];
+    auto load = [&](double2* p, double2* q, int at) {
 #pragma unroll
-    for (int e = 0; e < kB / 2; ++e) {
-      const double2 v = *reinterpret_cast<const double2*>(u + 2 * e);
-      const double2 w = *reinterpret_cast<const double2*>(y + 2 * e);
-      pr[2 * e] = v.x * w.x;
-      pr[2 * e + 1] = v.y * w.y;
-      a[e] = *reinterpret_cast<const double2*>(u + kB + 2 * e);
-      b[e] = *reinterpret_cast<const double2*>(y + kB + 2 * e);
-    }
-    // pr: products of block [i - 2 kB, i - kB); a, b: operands of [i - kB, i)
-    for (i = 2 * kB; i + kB <= m; i += kB) {
+      for (int e = 0; e < kB / 2; ++e) p[e] = *reinterpret_cast<const double2*>(u + at + 2 * e);
+#pragma unroll
+      for (int e = 0; e < kB / 2; ++e) q[e] = *reinterpret_cast<const double2*>(y + at + 2 * e);
+    };
+    auto sum = [&](const double2* p, const double2* q) {
 #pragma unroll
       for (int e = 0; e < kB / 2; ++e) {
-        x += pr[2 * e];
-        pr[2 * e] = a[e].x * b[e].x;
-        x += pr[2 * e + 1];
-        pr[2 * e + 1] = a[e].y * b[e].y;
-        a[e] = *reinterpret_cast<const double2*>(u + i + 2 * e);
-        b[e] = *reinterpret_cast<const double2*>(y + i + 2 * e);
+        x += p[e].x * q[e].x;
+        x += p[e].y * q[e].y;
       }
-    }
-#pragma unroll
-    for (int e = 0; e < kB; ++e) x += pr[e];
-#pragma unroll
-    for (int e = 0; e < kB / 2; ++e) {
-      x += a[e].x * b[e].x;
-      x += a[e].y * b[e].y;
+    };
+    load(a, b, 0);
+#pragma unroll 1
+    for (; i + 2 * kB <= m; i += 2 * kB) {
+      load(v, w, i + kB);
+      sum(a, b);
+      load(a, b, i + 3 * kB <= m ? i + 2 * kB : 0);
+      sum(v, w);
     }
   }
   for (; i < m; ++i) x += u[i] * y[i];
