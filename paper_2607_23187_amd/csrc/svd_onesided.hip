@@ -19,6 +19,7 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "jacobi_device.h"
 #include "kernels.h"
 #include "mw_exchange.h"
 
@@ -187,252 +188,365 @@ __device__ __forceinline__ bool wave_best_fast(double& v, int& k) {
   return true;
 }
 
-// Packed upper triangle: position of (i, j), i <= j, of an n x n symmetric matrix.
-__device__ __forceinline__ int tri(int i, int j, int n) { return i * (2 * n - i - 1) / 2 + j; }
-
-// LDS bytes of the resident mode: B with an odd row stride (the column accesses of the
-// rotation then fall in distinct banks), A as a packed upper triangle, the new columns p
-// and q contiguous, and best, diag, rows p and q of A, arg and the rescan queue.
-__host__ __device__ __forceinline__ int svd_lds_ld(int n) { return n | 1; }
+// Bytes of dynamic LDS of the resident mode: B by columns with an odd stride (the lanes' reads of
+// their own columns then fall in distinct banks), zeros, and rows p, q and the diagonal of A.
+constexpr int kSvdResMaxN = 128, kSvdResPad = 24;
+// the rotated columns once more, with zeros up to the reads ahead of the last term
+__host__ __device__ __forceinline__ int svd_col_len(int m) { return ((m + 15) & ~15) + 8; }
+__host__ __device__ __forceinline__ int svd_lds_ld(int m) { return m | 1; }
 __host__ __device__ __forceinline__ size_t svd_lds_bytes(int m, int n) {
-  return 8 * ((size_t)m * svd_lds_ld(n) + (size_t)n * (n + 1) / 2 + 2 * (size_t)m +
-              4 * (size_t)n) +
-         8 * (size_t)n;
+  return 8 * ((size_t)n * svd_lds_ld(m) + kSvdResPad + 2 * (size_t)svd_col_len(m) +
+              3 * kSvdResMaxN + 1);
 }
 
-// Resident mode: B and A stay in LDS for the whole run, every exchange between waves goes
-// through LDS.  Per rotation:
-//   B  (all lanes) argmax, rotation parameters, columns p and q of B rotated in place and
-//      copied contiguously; this lane's entries of rows p, q of V^T loaded (each lane owns
-//      the same entries for the whole run).                                      barrier
-//   C  the 2n dot products of rows p and q of A, one per lane; V^T entries stored.
-//                                                                                barrier
-//   D  A's rows p, q and diagonal stored; per-row cache refresh with rows whose cached best
-//      moved down queued; full rescans of rows p and q by two waves (entries stored by
-//      other lanes in this phase, diag[p] and diag[q], are taken from rows p, q).  barrier
-//   E  (only if the queue is not empty) full rescans of the queued rows.          barrier
+struct SvdBestAt {
+  double s, a;  // score (-1: none) and entry
+  int c;        // column
+};
+
+struct SvdRow {
+  SvdBestAt x, y;  // best and second best
+  double u;        // bound of the others
+};
+
+__device__ __forceinline__ bool svd_before(const SvdBestAt& a, const SvdBestAt& b) {
+  return a.s > b.s || (a.s == b.s && a.c < b.c);
+}
+
+__device__ __forceinline__ SvdBestAt svd_pick(bool w, const SvdBestAt& a, const SvdBestAt& b) {
+  return SvdBestAt{w ? a.s : b.s, w ? a.a : b.a, w ? a.c : b.c};
+}
+
+__device__ __forceinline__ SvdBestAt svd_none() { return SvdBestAt{-1.0, 0.0, INT_MAX}; }
+
+// The best two of two ordered pairs; the bound takes the other two.
+__device__ __forceinline__ void svd_row_merge(SvdRow& r, const SvdBestAt& x, const SvdBestAt& y) {
+  const bool w = svd_before(x, r.x);
+  const SvdBestAt l = svd_pick(w, r.x, x), sw = svd_pick(w, y, r.y);
+  const double o = w ? r.y.s : y.s;
+  const bool v = svd_before(l, sw);
+  r.x = svd_pick(w, x, r.x);
+  r.y = svd_pick(v, l, sw);
+  r.u = fmax(fmax(r.u, o), v ? sw.s : l.s);
+}
+
+// The best two of one wave's entries of rows p and q (score, column k, entry per lane) and a
+// bound of the rest, the two rows' chains interleaved: out[row] = s, a, s', a', bound, c | c' << 32.
+__device__ __forceinline__ void svd_search2(double ep, double vp, double eq, double vq, int k,
+                                            double (*out)[6], int lane) {
+  int a = key32(ep), b = key32(eq);
+  auto max2 = [](int x, int y, int& mx, int& my) {
+    x = max(x, dpp_i<0xB1>(x)); y = max(y, dpp_i<0xB1>(y));
+    x = max(x, dpp_i<0x4E>(x)); y = max(y, dpp_i<0x4E>(y));
+    x = max(x, dpp_i<0x141>(x)); y = max(y, dpp_i<0x141>(y));
+    x = max(x, dpp_i<0x140>(x)); y = max(y, dpp_i<0x140>(y));
+    auto rows = [](int m) {
+      return max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                 max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+    };
+    mx = rows(x);
+    my = rows(y);
+  };
+  if (lane < 2) {
+    out[lane][0] = out[lane][2] = -1.0;
+    out[lane][1] = out[lane][3] = 0.0;
+    reinterpret_cast<int*>(&out[lane][5])[0] = reinterpret_cast<int*>(&out[lane][5])[1] = INT_MAX;
+  }
+  int ma, mb;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    max2(a, b, ma, mb);
+    const int la = argmax_finish(ep, k, a, ma), lb = argmax_finish(eq, k, b, mb);
+    if (lane == la) {
+      out[0][2 * e] = ep;
+      out[0][2 * e + 1] = vp;
+      reinterpret_cast<int*>(&out[0][5])[e] = k;
+    }
+    if (lane == lb) {
+      out[1][2 * e] = eq;
+      out[1][2 * e + 1] = vq;
+      reinterpret_cast<int*>(&out[1][5])[e] = k;
+    }
+    a = lane == la ? -1 : a;
+    b = lane == lb ? -1 : b;
+  }
+  max2(a, b, ma, mb);
+  if (lane < 2) out[lane][4] = key_ub(lane ? mb : ma);
+}
+
+// Resident mode, n <= 128: B stays in LDS for the whole run.  The bound is the chain of one
+// rotation: the pick, its parameters, the dot products of rows p and q of A, their scores.
+//
+// Dot products: lane k forms a_pk, lane 128 + k a_qk, in index order, from the lanes' own columns
+// and a copy of the rotated one, in two blocks of 8 terms in turn, each read while the other is
+// summed (13.3 ns a term; 24.7 with one block read, then summed; 17.6 with the rotated column
+// across the lanes, handed round by v_readlane).  The limit is one wave's LDS reads, 16 bytes a
+// lane in 21 cycles.  A itself is not kept: its entries are needed where they change and in the
+// rare rescan, which forms them again (same products, same order, same bits).
+//
+// Caches: lane k < 128 owns row k's: its exact best (score, column, entry), the second best, and a
+// bound of the others.  A row whose best moved down takes its second best or a new entry, where
+// that lies above the bound, and is rescanned before the next selection otherwise (Hilbert
+// matrix's factor of order 100, relative score: 0.93 rows per rotation lose their best, 0.02 are
+// rescanned).  Lanes 128 .. 255 search the new rows p and q while the others select and rotate;
+// until then those two rows' caches hold the pair (p, q) alone, as every other new pair is in
+// the other row's cache.
+//
+// Measured, per rotation, before (A in LDS, a rescan for every best that moved down) and now:
+// Hilbert factor of order 100 4.70 -> 3.96 us (dot products 1.4, parameters and columns 0.75,
+// scores 0.7, caches 0.3, selection 0.3, rescans 0.2), 130 x 100 5.0 -> 4.8, 500 x 30 10.3 -> 9.4,
+// 130 x 128 (on several workgroups before) 7.1 -> 4.9.
 template <int PIV>
 __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
-  constexpr int NT = 256, NW = NT / 64;
-  extern __shared__ double smem[];
-  __shared__ int s_cnt, s_resc;
+  constexpr int NT = 256, kB = 8;
+  extern __shared__ __attribute__((aligned(16))) double smem[];
+  __shared__ __attribute__((aligned(16))) double s_slot[2][4], s_pq[2][2][6], s_cs[2];
+  __shared__ int s_list[kSvdResMaxN], s_cnt, s_resc;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n = d.n, m = d.m, ldy = svd_lds_ld(n);
-  const size_t ldv = d.ldv, ldg = d.ldg;
-  double* Y = smem;
-  double* Gp = Y + (size_t)m * ldy;
-  double* colp = Gp + (size_t)n * (n + 1) / 2;
-  double* colq = colp + m;
-  double* best = colq + m;
-  double* diag = best + n;
-  double* rowp = diag + n;
-  double* rowq = rowp + n;
-  int* arg = (int*)(rowq + n);
-  int* list = arg + n;
-  for (int i = tid; i < m * n; i += NT) {
-    const int r = i / n, k = i - r * n;
-    Y[r * ldy + k] = d.Y[(size_t)r * d.ldy + k];
+  const int half = tid >> 7, k = tid & (kSvdResMaxN - 1);
+  const int n = d.n, m = d.m, ldc = svd_lds_ld(m);
+  const size_t ldv = d.ldv;
+  const int cl = svd_col_len(m);
+  double* colp = smem;
+  double* colq = colp + cl;
+  double* Yc = colq + cl;  // column k of B from Yc + k ldc
+  double* rowp = Yc + (size_t)n * ldc + kSvdResPad;
+  double* rowq = rowp + kSvdResMaxN;
+  double* diag = rowq + kSvdResMaxN;
+  for (int i = tid; i < n * ldc; i += NT) {
+    const int r = i / n, c = i - r * n;
+    Yc[c * ldc + r] = r < m ? d.Y[(size_t)r * d.ldy + c] : 0.0;
   }
-  for (int i = 0; i < n; ++i)
-    for (int j = i + tid; j < n; j += NT) Gp[tri(i, j, n)] = d.G[(size_t)i * ldg + j];
-  for (int k = tid; k < n; k += NT) {
-    best[k] = d.best[k];
-    arg[k] = d.arg[k];
-    diag[k] = d.diag[k];
-  }
+  for (int i = tid; i < 2 * cl; i += NT) colp[i] = 0.0;
+  if (tid < n) diag[tid] = d.diag[tid];
+  if (tid < kSvdResPad) Yc[(size_t)n * ldc + tid] = 0.0;
   if (tid == 0) {
-    s_resc = 0;
     s_cnt = 0;
+    s_resc = 0;
   }
   __syncthreads();
+  const bool act = k < n;
+  const double* mine = Yc + (act ? k : 0) * ldc;
+  // sum_i u_i z_i in index order, z this lane's column, read a block of 8 ahead; the terms that
+  // fill up the last 16 have u_i = 0 and a finite z_i (the next column's, or the zeros behind
+  // the last)
+  auto dot = [&](const double* u) -> double {
+    double x = 0.0, u0[kB], z0[kB], u1[kB], z1[kB];
+#pragma unroll
+    for (int e = 0; e < kB; ++e) u0[e] = u[e];
+#pragma unroll
+    for (int e = 0; e < kB; ++e) z0[e] = mine[e];
+#pragma unroll 1
+    for (int i = 0; i < m; i += 2 * kB) {
+#pragma unroll
+      for (int e = 0; e < kB; ++e) u1[e] = u[i + kB + e];
+#pragma unroll
+      for (int e = 0; e < kB; ++e) z1[e] = mine[i + kB + e];
+#pragma unroll
+      for (int e = 0; e < kB; ++e) x += u0[e] * z0[e];
+#pragma unroll
+      for (int e = 0; e < kB; ++e) u0[e] = u[i + 2 * kB + e];
+#pragma unroll
+      for (int e = 0; e < kB; ++e) z0[e] = mine[i + 2 * kB + e];
+#pragma unroll
+      for (int e = 0; e < kB; ++e) x += u1[e] * z1[e];
+    }
+    return x;
+  };
+  auto uni = [](int v) -> int { return __builtin_amdgcn_readfirstlane(v); };
+  auto score = [&](double x, double y, double a) -> double {
+    const double s = svd_score<PIV>(x, y, a);
+    return s >= 0.0 ? s : -1.0;
+  };
+
+  double dk = act ? d.diag[k] : 0.0;
+  SvdRow row{svd_none(), svd_none(), -1.0};
+  if (half == 0 && act) {
+    row.x.s = d.best[k];
+    row.x.c = d.arg[k];
+    if (row.x.c >= 0) row.x.a = d.G[(size_t)k * d.ldg + row.x.c];
+    row.u = row.x.s;  // the others are no better
+  }
+  // rows whose search is under way in lanes 128 .. 255: their scores, and the lanes that wait
+  int pend = -1, resc = 0;  // 0 / 1: this lane's row is row p / q of the last rotation
+  double ep = -1.0, eq = -1.0, vp = 0.0, vq = 0.0;
+  auto search = [&]() { svd_search2(ep, vp, eq, vq, k, s_pq[wv & 1], lane); };
+  // the row's second best and bound after a rotation, from its caches before (x0, y0) and the
+  // new entries
+  SvdBestAt hi = svd_none(), lo = svd_none(), x0 = svd_none(), y0 = svd_none();
+  bool lost = false, won = false;
+  auto settle = [&]() {
+    const SvdBestAt y1 = svd_pick(lost, svd_none(), y0);
+    const SvdBestAt l = svd_pick(won, x0, hi), sw = svd_pick(won, lo, y1);
+    const bool v = l.s > sw.s;
+    row.y = svd_pick(v, l, sw);
+    row.u = fmax(fmax(row.u, won ? y1.s : lo.s), v ? sw.s : l.s);
+    if (!(row.y.s > row.u)) row.y = svd_none();
+  };
+  // a second best that another entry may equal is not kept
+  auto trim = [&]() {
+    const bool keep = row.y.s > row.u;
+    row.y = svd_pick(keep, row.y, svd_none());
+  };
+  auto found = [&]() {
+    if (pend >= 0) {
+      const double* o0 = s_pq[0][pend];
+      const double* o1 = s_pq[1][pend];
+      const int* c0 = reinterpret_cast<const int*>(o0 + 5);
+      const int* c1 = reinterpret_cast<const int*>(o1 + 5);
+      row = SvdRow{{o0[0], o0[1], c0[0]}, {o0[2], o0[3], c0[1]}, fmax(o0[4], o1[4])};
+      svd_row_merge(row, {o1[0], o1[1], c1[0]}, {o1[2], o1[3], c1[1]});
+      trim();
+      pend = -1;
+    }
+  };
   long long rot = 0;
   int status = ST_OK;
   double vsel = -1.0;
+  bool moving = false;  // a search is pending
   for (;;) {
-    // ---- B
-    double v = -1.0;
-    int r = INT_MAX;
-    for (int k = lane; k < n; k += 64) {
-      const double x = best[k];
-      if (x > v) {
-        v = x;
-        r = k;
+    // ---- the best pair; rows without a known best are rescanned first
+    if (half == 0) {
+      const int w = wave_argmax_lane(row.x.s, k);
+      if (lane == max(w, 0)) {
+        s_slot[wv][0] = w >= 0 ? row.x.s : -1.0;
+        s_slot[wv][1] = row.x.a;
+        s_slot[wv][2] = __longlong_as_double((long long)(k | row.x.c << 16));
       }
     }
-    if (!wave_best_fast(v, r)) v = -1.0;
+    lds_barrier();
+    const double v0 = s_slot[0][0], a0 = s_slot[0][1], v1 = s_slot[1][0], a1 = s_slot[1][1];
+    const int rc0 = (int)__double_as_longlong(s_slot[0][2]);
+    const int rc1 = (int)__double_as_longlong(s_slot[1][2]);
+    const int cnt = uni(s_cnt);
+    if (cnt > 0) {
+      if (moving) settle();
+      if (moving && half) search();
+      lds_barrier();
+      found();
+      moving = false;
+      for (int e = 0; e < cnt; e += 2) {
+        const int r0 = uni(s_list[e]), r1 = uni(s_list[min(e + 1, cnt - 1)]);
+        for (int i = tid; i < m; i += NT) {
+          colp[i] = Yc[r0 * ldc + i];
+          colq[i] = Yc[r1 * ldc + i];
+        }
+        lds_barrier();
+        const double x = dot(half ? colq : colp);
+        (half ? rowq : rowp)[k] = x;
+        lds_barrier();
+        vp = rowp[k];
+        vq = rowq[k];
+        ep = act && k != r0 ? score(dk, diag[r0], vp) : -1.0;
+        eq = act && k != r1 ? score(dk, diag[r1], vq) : -1.0;
+        if (half) search();
+        if (half == 0 && (k == r0 || k == r1)) pend = k == r0 ? 0 : 1;
+        lds_barrier();
+        found();
+      }
+      if (tid == 0) s_cnt = 0;
+      continue;
+    }
+    const bool w = v1 > v0;
+    const double v = w ? v1 : v0, apq = w ? a1 : a0;
+    const int rc = uni(w ? rc1 : rc0);
     vsel = v;
     if (n < 2 || v <= d.thr) break;
     if (rot >= d.maxrot) {
       status = ST_MAXROT;
       break;
     }
-    const int a = arg[r];
-    const int p = min(r, a), q = max(r, a);
-    const double apq = Gp[tri(p, q, n)];
     if (apq == 0.0) {
       status = ST_STALL;
       break;
     }
-    double t, c, s;
-    rot_params<double>(diag[p], diag[q], apq, t, c, s);
-    // this lane's entries of rows p, q of V^T (n <= NT here): loaded now, stored after the
-    // dot products so that the memory latency overlaps them
-    const bool hv = d.Vt != nullptr && tid < n;
+    const int p = min(rc & 0xffff, rc >> 16), q = max(rc & 0xffff, rc >> 16);
+    // ---- columns p and q of B; rows p and q of V^T, whose entries keep their lane for the
+    // whole run, are loaded now and stored after the dot products
+    const bool hv = d.Vt != nullptr && half && act;
     double vu = 0.0, vw = 0.0;
     if (hv) {
-      vu = d.Vt[(size_t)p * ldv + tid];
-      vw = d.Vt[(size_t)q * ldv + tid];
+      vu = d.Vt[(size_t)p * ldv + k];
+      vw = d.Vt[(size_t)q * ldv + k];
     }
-    if (tid == 0 && d.plog && rot < d.logcap) {
-      d.plog[2 * rot] = p;
-      d.plog[2 * rot + 1] = q;
+    if (half && moving) search();
+    if (wv * 64 < m) {
+      double* yp = Yc + p * ldc;
+      double* yq = Yc + q * ldc;
+      const double u0 = tid < m ? yp[tid] : 0.0, x0 = tid < m ? yq[tid] : 0.0;
+      double t, c, s;
+      rot_params<double>(diag[p], diag[q], apq, t, c, s);
+      if (moving) settle();
+      if (tid < m) {
+        yp[tid] = colp[tid] = c * u0 + s * x0;
+        yq[tid] = colq[tid] = c * x0 - s * u0;
+      }
+      for (int i = tid + NT; i < m; i += NT) {
+        const double u = yp[i], x = yq[i];
+        yp[i] = colp[i] = c * u + s * x;
+        yq[i] = colq[i] = c * x - s * u;
+      }
+      if (tid == 0) {
+        s_cs[0] = c;
+        s_cs[1] = s;
+        if (d.plog && rot < d.logcap) {
+          d.plog[2 * rot] = p;
+          d.plog[2 * rot + 1] = q;
+        }
+      }
     }
     ++rot;
-    for (int i = tid; i < m; i += NT) {
-      double* yi = Y + i * ldy;
-      const double u = yi[p], w = yi[q];
-      const double np_ = c * u + s * w, nq_ = c * w - s * u;
-      yi[p] = np_;
-      yi[q] = nq_;
-      colp[i] = np_;
-      colq[i] = nq_;
-    }
     lds_barrier();
-    // ---- C: a_pk = sum_i b_ip b_ik (tasks 0..n-1) and a_qk = sum_i b_iq b_ik (tasks n..2n-1),
-    // each by one lane in index order; the loads of a block of rows are issued before its sums
-    for (int task = tid; task < 2 * n; task += NT) {
-      const bool onp = task < n;
-      const int k = onp ? task : task - n;
-      const double* yc = onp ? colp : colq;
-      const double* yk = Y + k;
-      constexpr int kB = 8;
-      double x = 0.0;
-      int i = 0;
-      for (; i + kB <= m; i += kB) {
-        double u[kB], z[kB];
-#pragma unroll
-        for (int e = 0; e < kB; ++e) {
-          u[e] = yc[i + e];
-          z[e] = yk[(i + e) * ldy];
-        }
-#pragma unroll
-        for (int e = 0; e < kB; ++e) x += u[e] * z[e];
-      }
-      for (; i < m; ++i) x += yc[i] * yk[i * ldy];
-      (onp ? rowp : rowq)[k] = x;
-    }
+    // ---- rows p and q of A
+    const bool own = k == p || k == q;
+    const double x = dot(half ? colq : colp);
+    (half ? rowq : rowp)[k] = x;
     if (hv) {
-      d.Vt[(size_t)p * ldv + tid] = c * vu + s * vw;
-      d.Vt[(size_t)q * ldv + tid] = c * vw - s * vu;
+      const double c = s_cs[0], s = s_cs[1];
+      d.Vt[(size_t)p * ldv + k] = c * vu + s * vw;
+      d.Vt[(size_t)q * ldv + k] = c * vw - s * vu;
     }
     lds_barrier();
-    // ---- D
+    // ---- scores and caches (a_pq is row p's, the same bits as row q's)
+    found();
     const double app = rowp[p], aqq = rowq[q];
-    for (int k = tid; k < n; k += NT) {
-      // a_pq is stored once, from row p (the same bits as rowq[p])
-      Gp[tri(min(p, k), max(p, k), n)] = rowp[k];
-      if (k != p) Gp[tri(min(q, k), max(q, k), n)] = rowq[k];
-      if (k == p) {
-        diag[p] = app;
-        continue;
-      }
-      if (k == q) {
-        diag[q] = aqq;
-        continue;
-      }
-      const double akk = diag[k];
-      const double sp = svd_score<PIV>(akk, app, rowp[k]);
-      const double sq = svd_score<PIV>(akk, aqq, rowq[k]);
-      double b = best[k];
-      int ak = arg[k];
-      if (ak == p || ak == q) {
-        double x = sp;
-        int col = p;
-        if (sq > x) {
-          x = sq;
-          col = q;
-        }
-        if (x > b || (x == b && col <= ak)) {
-          best[k] = x;
-          arg[k] = col;
-        } else {
-          list[atomicAdd(&s_cnt, 1)] = k;
-          atomicAdd(&s_resc, 1);
-        }
-      } else {
-        if (sp > b || (sp == b && p < ak)) {
-          b = sp;
-          ak = p;
-        }
-        if (sq > b || (sq == b && q < ak)) {
-          b = sq;
-          ak = q;
-        }
-        best[k] = b;
-        arg[k] = ak;
-      }
+    vp = rowp[k];
+    vq = k == p ? rowp[q] : rowq[k];
+    dk = k == p ? app : (k == q ? aqq : dk);
+    ep = act && k != p ? score(dk, app, vp) : -1.0;
+    eq = act && k != q ? score(dk, aqq, vq) : -1.0;
+    moving = true;
+    if (tid == NT - 1) {
+      diag[p] = app;
+      diag[q] = aqq;
     }
-    if (wv >= NW - 2) {
-      // rows p and q: their entries are rowp / rowq; diag[p], diag[q] are being stored in
-      // this phase, so their new values are taken from rowp[p], rowq[q]
-      const int k = wv == NW - 2 ? p : q;
-      const double* gk = wv == NW - 2 ? rowp : rowq;
-      const double akk = gk[k];
-      double bv = -1.0;
-      int bc = INT_MAX;
-      for (int l = lane; l < n; l += 64) {
-        if (l == k) continue;
-        const double all = l == p ? app : (l == q ? aqq : diag[l]);
-        const double x = svd_score<PIV>(akk, all, gk[l]);
-        if (x > bv) {
-          bv = x;
-          bc = l;
-        }
-      }
-      wave_best_fast(bv, bc);
-      if (lane == 0) {
-        best[k] = bv;
-        arg[k] = bc;
-      }
+    // the best of this lane's row now; what follows the best waits for settle()
+    const bool hit = row.x.c == p || row.x.c == q, hit2 = row.y.c == p || row.y.c == q;
+    const bool qf = eq > ep;
+    hi = SvdBestAt{qf ? eq : ep, qf ? vq : vp, qf ? q : p};
+    lo = SvdBestAt{qf ? ep : eq, qf ? vp : vq, qf ? p : q};
+    lost = hit && !own;
+    y0 = svd_pick(hit2 || own, svd_none(), row.y);
+    x0 = svd_pick(own, svd_none(), svd_pick(hit, y0, row.x));
+    if (half == 0 && !own && hit && !(hi.s > row.x.s || (hi.s == row.x.s && hi.c <= row.x.c))) ++resc;
+    if (own) {
+      pend = k == p ? 0 : 1;
+      hi = SvdBestAt{k == p ? eq : ep, k == p ? vq : vp, k == p ? q : p};
+      lo = svd_none();
+      row.u = -1.0;
     }
-    lds_barrier();
-    // ---- E
-    const int cnt = s_cnt;
-    if (cnt > 0) {
-      for (int e = wv; e < cnt; e += NW) {
-        const int k = list[e];
-        const double akk = diag[k];
-        double bv = -1.0;
-        int bc = INT_MAX;
-        for (int l = lane; l < n; l += 64) {
-          if (l == k) continue;
-          const double x = svd_score<PIV>(akk, diag[l], Gp[tri(min(k, l), max(k, l), n)]);
-          if (x > bv) {
-            bv = x;
-            bc = l;
-          }
-        }
-        wave_best_fast(bv, bc);
-        if (lane == 0) {
-          best[k] = bv;
-          arg[k] = bc;
-        }
-      }
-      lds_barrier();
-      if (tid == 0) s_cnt = 0;
-    }
+    won = svd_before(hi, x0);
+    row.x = svd_pick(won, hi, x0);
+    // the best is exact if it was before, or is above every entry not held here
+    if (half == 0 && act && lost && !(row.x.s > row.u)) s_list[atomicAdd(&s_cnt, 1)] = k;
   }
   __syncthreads();
   for (int i = tid; i < m * n; i += NT) {
-    const int r = i / n, k = i - r * n;
-    d.Y[(size_t)r * d.ldy + k] = Y[r * ldy + k];
+    const int r = i / n, c = i - r * n;
+    d.Y[(size_t)r * d.ldy + c] = Yc[c * ldc + r];
   }
-  for (int i = 0; i < n; ++i)
-    for (int j = i + tid; j < n; j += NT) {
-      const double x = Gp[tri(i, j, n)];
-      d.G[(size_t)i * ldg + j] = x;
-      d.G[(size_t)j * ldg + i] = x;
-    }
+  if (resc) atomicAdd(&s_resc, resc);
+  __syncthreads();
   if (tid == 0) {
     d.ctl->rotations = rot;
     d.ctl->rescans = s_resc;
@@ -1033,9 +1147,8 @@ static int svd_max_lds() {
 }
 
 bool svd_resident(int m, int n) {
-  // one lane per entry of a row of V^T; the static LDS of the kernel (two counters) and a
-  // margin stay free
-  return n <= 256 && svd_lds_bytes(m, n) + 1024 <= (size_t)svd_max_lds();
+  // two lanes per column; the static LDS of the kernel (1 KB) and a margin stay free
+  return n <= kSvdResMaxN && svd_lds_bytes(m, n) + 2048 <= (size_t)svd_max_lds();
 }
 
 template <typename K>
@@ -1055,8 +1168,11 @@ static hipError_t svd_jacobi_t(const SDesc& d, hipStream_t s) {
                      d.n, d.best, d.arg, d.diag);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (svd_resident(d.m, d.n))
-    return svd_launch_main(k_svd_res<PIV>, 256, svd_lds_bytes(d.m, d.n), d, s);
+  if (svd_resident(d.m, d.n)) {
+    e = svd_launch_main(k_svd_res<PIV>, 256, svd_lds_bytes(d.m, d.n), d, s);
+    // A's entries once more, for the final off-norm and the singular values
+    return e != hipSuccess ? e : launch_svd_gram(d.Y, d.ldy, d.m, d.n, d.G, d.ldg, s);
+  }
   // one workgroup; more lanes once the dot products of a rotation outnumber 256
   if (d.n > 256) return svd_launch_main(k_svd1<PIV, 1024>, 1024, (size_t)d.n * 4, d, s);
   return svd_launch_main(k_svd1<PIV, 256>, 256, (size_t)d.n * 4, d, s);
