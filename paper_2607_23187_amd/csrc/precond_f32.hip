@@ -239,19 +239,19 @@ __device__ __forceinline__ RotF fetch_rot(const RotF& x, int src) {
 }
 
 // An inner round is one phase: the pairs of the round are disjoint, so J^T S J is, block by
-// block, X_bc -> J_b^T X_bc J_c over the 2 x 2 blocks of pair b's rows and pair c's columns.
-// Lane l of wave w owns column pair c = l mod 32 and row pairs kb = 2 w + l / 32 and
-// kb + PM / 4: the blocks (kb, c), (kb + PM / 4, c), and columns 4 (c mod 16) .. + 3 of rows
-// p, q of U^T for one of the two row pairs.  The 32 lanes of a half wave share a row pair,
-// so their reads and writes of S fall on 32 consecutive columns (32 banks) in the rounds
-// that pair the two blocks (with the former layout, two column pairs per lane, they met
-// two-way bank conflicts: batched solve 66 -> 62 ms).  A lane evaluates its column pair's rotation itself and reads the row pairs'
-// from the lanes that evaluated them (the same instructions on the same values in every
-// lane, so all lanes agree).  S is double-buffered: a round reads one buffer and writes the
-// other, and a single barrier separates rounds.  S stays symmetric up to rounding; its upper
-// triangle is the one used.  (Used for 32-row blocks: measured against the two-phase form,
-// n = 4096 FP32 stage 243 -> 236 ms, batches 272 -> 261 ms; for 16-row blocks, two waves per
-// subproblem, the two-phase form is faster, n = 1024 27.8 vs 34.7 ms.)
+// block, X_bc -> J_b^T X_bc J_c over the 2 x 2 blocks of pair b's rows and pair c's columns.  S is
+// symmetric, so only one of X_bc and X_cb is formed, and only the upper triangle of S is kept.
+// The 16 x 32 threads each hold one block, of pairs b = thread mod 32 and c = b + 1 + thread / 32
+// (mod 32), and four columns of rows p, q of U^T of pair b.  A lane evaluates pair b's rotation
+// and takes pair c's cosine and sine from the lane of its half wave that evaluated it (the same
+// instructions on the same values, so all lanes agree).  Reads and writes of a half wave walk
+// down a diagonal of S, one bank apart from row to row.  S is double-buffered: a round reads one
+// buffer and writes the other, and a single barrier separates rounds.  What bounds it is LDS
+// traffic (several workgroups on a CU): 17 accesses a wave and round and four of 16 bytes a lane;
+// with all blocks X_bc, two per thread, they were 35 and four.  FP32 stage before and now:
+// batch of 512 (n to 512) 47.9 -> 40.8 ms, of 1024 (n to 128) 8.2 -> 6.7, n = 2048 38.8 -> 32.5.
+// Both buffers in the two triangles of one, for four workgroups on a CU instead of three, is no
+// faster (41.6 ms).
 template <int PB>
 __device__ __forceinline__ void solve_body_blocks(float (*S)[Blk<PB>::PL], float (*W)[Blk<PB>::PL],
                                            float (*Ut)[Blk<PB>::PL], const float* Ain,
@@ -268,44 +268,41 @@ __device__ __forceinline__ void solve_body_blocks(float (*S)[Blk<PB>::PL], float
     set_identity<PB>(Ut);
     __syncthreads();
   }
-  const int lane = tid & 63, c = lane & 31;
-  const int kb0 = 2 * (tid >> 6) + (lane >> 5);
+  // pairs b and c = b + d, d = 1 .. 16 (d = 16: the same two pairs twice, stored once)
+  const int lane = tid & 63, b = tid & 31, d = 1 + (tid >> 5), c = (b + d) & 31;
+  const int from = (lane & 32) | c;  // the lane of this wave that evaluates pair c
+  const bool once = d < 16 || b < 16;
+  const int jb = 4 * (tid >> 5);
   const int nr = full ? PM - 1 : PB;
   float(*Sc)[PL] = S;
   float(*Sn)[PL] = W;
   float prev_off = 3.4e38f;
+  auto at = [](int i, int j) -> int { return min(i, j) * PL + max(i, j); };
   for (int sw = 0; sw < inner_max; ++sw) {
     for (int r = 0; r < nr; ++r) {
-      int pc, qc;
+      int pb, qb, pc, qc;
+      inner_pair<PB>(full, r, b, pb, qb);
       inner_pair<PB>(full, r, c, pc, qc);
-      const RotF rc = pair_rot<PL>(Sc, pc, qc);
-      int pb[2], qb[2];
-      RotF rb[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int kb = kb0 + h * (PM / 4);
-        inner_pair<PB>(full, r, kb, pb[h], qb[h]);
-        float x = Sc[pb[h]][pc], y = Sc[pb[h]][qc], z = Sc[qb[h]][pc], w = Sc[qb[h]][qc];
-        rb[h] = fetch_rot(rc, kb);
-        rot_block(rb[h], rc, kb == c, x, y, z, w);
-        Sn[pb[h]][pc] = x; Sn[pb[h]][qc] = y; Sn[qb[h]][pc] = z; Sn[qb[h]][qc] = w;
-      }
-      {
-        // rows p, q of U^T: lane c < 16 takes columns 4c .. 4c + 3 of the first row pair,
-        // lane c >= 16 those of the second
-        const int h = c >> 4, jb = 4 * (c & 15);
-        const RotF& ru = h ? rb[1] : rb[0];
-        const int pu = h ? pb[1] : pb[0], qu = h ? qb[1] : qb[0];
-        const float4 up = *reinterpret_cast<const float4*>(&Ut[pu][jb]);
-        const float4 uq = *reinterpret_cast<const float4*>(&Ut[qu][jb]);
-        float4 po, qo;
-        po.x = ru.c * up.x + ru.s * uq.x; qo.x = ru.c * uq.x - ru.s * up.x;
-        po.y = ru.c * up.y + ru.s * uq.y; qo.y = ru.c * uq.y - ru.s * up.y;
-        po.z = ru.c * up.z + ru.s * uq.z; qo.z = ru.c * uq.z - ru.s * up.z;
-        po.w = ru.c * up.w + ru.s * uq.w; qo.w = ru.c * uq.w - ru.s * up.w;
-        *reinterpret_cast<float4*>(&Ut[pu][jb]) = po;
-        *reinterpret_cast<float4*>(&Ut[qu][jb]) = qo;
-      }
+      const int ox = at(pb, pc), oy = at(pb, qc), oz = at(qb, pc), ow = at(qb, qc);
+      const float* Sr = &Sc[0][0];
+      float* Sw = &Sn[0][0];
+      float x = Sr[ox], y = Sr[oy], z = Sr[oz], w = Sr[ow];
+      const float4 up = *reinterpret_cast<const float4*>(&Ut[pb][jb]);
+      const float4 uq = *reinterpret_cast<const float4*>(&Ut[qb][jb]);
+      const RotF rb = pair_rot<PL>(Sc, pb, qb);
+      RotF rc;
+      rc.c = __shfl(rb.c, from);
+      rc.s = __shfl(rb.s, from);
+      rot_block(rb, rc, false, x, y, z, w);
+      if (once) { Sw[ox] = x; Sw[oy] = y; Sw[oz] = z; Sw[ow] = w; }
+      if (d == 1) { Sn[pb][pb] = rb.napp; Sn[pb][qb] = rb.z; Sn[qb][qb] = rb.naqq; }
+      float4 po, qo;
+      po.x = rb.c * up.x + rb.s * uq.x; qo.x = rb.c * uq.x - rb.s * up.x;
+      po.y = rb.c * up.y + rb.s * uq.y; qo.y = rb.c * uq.y - rb.s * up.y;
+      po.z = rb.c * up.z + rb.s * uq.z; qo.z = rb.c * uq.z - rb.s * up.z;
+      po.w = rb.c * up.w + rb.s * uq.w; qo.w = rb.c * uq.w - rb.s * up.w;
+      *reinterpret_cast<float4*>(&Ut[pb][jb]) = po;
+      *reinterpret_cast<float4*>(&Ut[qb][jb]) = qo;
       __syncthreads();
       float(*t)[PL] = Sc;
       Sc = Sn;
@@ -316,7 +313,8 @@ __device__ __forceinline__ void solve_body_blocks(float (*S)[Blk<PB>::PL], float
       float so = 0.0f, sd = 0.0f;
       for (int e = tid; e < PM * PM; e += NT) {
         int i = e / PM, j = e % PM;
-        float v = Sc[i][j] * Sc[i][j];
+        float v = Sc[min(i, j)][max(i, j)];
+        v *= v;
         if (i == j) sd += v; else so += v;
       }
       for (int o = 32; o > 0; o >>= 1) { so += __shfl_xor(so, o); sd += __shfl_xor(sd, o); }
@@ -329,25 +327,22 @@ __device__ __forceinline__ void solve_body_blocks(float (*S)[Blk<PB>::PL], float
       prev_off = off;
     }
   }
-  if (Sc != S) {  // the result ends in S (callers read it there)
+  if (Sc != S) {  // the result ends in S (callers read its upper triangle there)
     for (int e = tid; e < PM * PM; e += NT) {
       int i = e / PM, j = e % PM;
-      S[i][j] = Sc[i][j];
+      if (i <= j) S[i][j] = Sc[i][j];
     }
     __syncthreads();
   }
   store_solved<PB>(S, Ut, Uo, Aout, np, pr);
 }
 
-// The same in one 2 x 2 block per thread, for 16-row blocks (four waves, one to a SIMD): thread
-// (b, c) = (tid / 16, tid mod 16) holds the block of row pair b and column pair c and columns
-// 2 c, 2 c + 1 of rows p, q of U^T of pair b.  Latency bounds an inner round (few workgroups, a
-// chain of LDS reads, one rotation, LDS writes and a barrier), so every thread evaluates both
-// rotations itself from broadcast reads, without branches between them, and one barrier ends
-// the round.  With two waves and two phases (rows, then columns, a barrier after each) the FP32
-// stage took 18.5 ms at n = 1024, 7.8 at 512 and 2.75 at 203; now 16.1, 7.0 and 2.35.  What is
-// left of a round (16 us at n = 1024, 7.9 of them the 16 inner rounds) is 18 LDS accesses of each
-// wave per inner round.
+// The same for 16-row blocks (four waves, one to a SIMD).  Latency bounds an inner round (few
+// workgroups, a chain of LDS reads, one rotation, LDS writes and a barrier), so every thread
+// evaluates the rotations it needs itself from broadcast reads, without branches between them:
+// two waves hold the blocks of S, the other two the rows of U^T and the new diagonals.  FP32
+// stage with two waves and two phases (rows, then columns, a barrier after each) 18.5 ms at n =
+// 1024, 7.8 at 512; on four waves with all blocks X_bc 16.1 and 7.0; now 15.7 and 6.8.
 template <int PB>
 __device__ __forceinline__ void solve_body_quads(float (*S)[Blk<PB>::PL], float (*W)[Blk<PB>::PL],
                                                  float (*Ut)[Blk<PB>::PL], const float* Ain,
@@ -364,30 +359,48 @@ __device__ __forceinline__ void solve_body_quads(float (*S)[Blk<PB>::PL], float 
     set_identity<PB>(Ut);
     __syncthreads();
   }
-  const int b = tid >> 4, c = tid & 15;
+  // the first two waves: blocks of pairs b and c = b + d, d = 1 .. 8 (d = 8: the same two pairs
+  // twice, stored once); the other two: columns jb .. jb + 3 of rows p, q of U^T of pair b
+  const bool onS = tid < 128;
+  const int b = tid & 15, d = 1 + ((tid & 127) >> 4), c = (b + d) & 15;
+  const bool once = d < 8 || b < 8;
+  const int jb = 4 * (d - 1);
   const int nr = full ? PM - 1 : PB;
   float(*Sc)[PL] = S;
   float(*Sn)[PL] = W;
   float prev_off = 3.4e38f;
+  auto at = [](int i, int j) -> int { return min(i, j) * PL + max(i, j); };
   for (int sw = 0; sw < inner_max; ++sw) {
     for (int r = 0; r < nr; ++r) {
-      int pb, qb, pc, qc;
+      int pb, qb;
       inner_pair<PB>(full, r, b, pb, qb);
-      inner_pair<PB>(full, r, c, pc, qc);
-      float x = Sc[pb][pc], y = Sc[pb][qc], z = Sc[qb][pc], w = Sc[qb][qc];
-      const float2 up = *reinterpret_cast<const float2*>(&Ut[pb][2 * c]);
-      const float2 uq = *reinterpret_cast<const float2*>(&Ut[qb][2 * c]);
-      const float bpp = Sc[pb][pb], bqq = Sc[qb][qb], bpq = Sc[pb][qb];
-      const float cpp = Sc[pc][pc], cqq = Sc[qc][qc], cpq = Sc[pc][qc];
-      const RotF rb = entry_rot(bpp, bqq, bpq);
-      const RotF rc = entry_rot(cpp, cqq, cpq);
-      rot_block(rb, rc, b == c, x, y, z, w);
-      Sn[pb][pc] = x; Sn[pb][qc] = y; Sn[qb][pc] = z; Sn[qb][qc] = w;
-      float2 po, qo;
-      po.x = rb.c * up.x + rb.s * uq.x; qo.x = rb.c * uq.x - rb.s * up.x;
-      po.y = rb.c * up.y + rb.s * uq.y; qo.y = rb.c * uq.y - rb.s * up.y;
-      *reinterpret_cast<float2*>(&Ut[pb][2 * c]) = po;
-      *reinterpret_cast<float2*>(&Ut[qb][2 * c]) = qo;
+      if (onS) {
+        int pc, qc;
+        inner_pair<PB>(full, r, c, pc, qc);
+        const int ox = at(pb, pc), oy = at(pb, qc), oz = at(qb, pc), ow = at(qb, qc);
+        const float* Sr = &Sc[0][0];
+        float* Sw = &Sn[0][0];
+        const float bpp = Sc[pb][pb], bqq = Sc[qb][qb], bpq = Sc[pb][qb];
+        const float cpp = Sc[pc][pc], cqq = Sc[qc][qc], cpq = Sc[pc][qc];
+        float x = Sr[ox], y = Sr[oy], z = Sr[oz], w = Sr[ow];
+        const RotF rb = entry_rot(bpp, bqq, bpq);
+        const RotF rc = entry_rot(cpp, cqq, cpq);
+        rot_block(rb, rc, false, x, y, z, w);
+        if (once) { Sw[ox] = x; Sw[oy] = y; Sw[oz] = z; Sw[ow] = w; }
+      } else {
+        const float bpp = Sc[pb][pb], bqq = Sc[qb][qb], bpq = Sc[pb][qb];
+        const float4 up = *reinterpret_cast<const float4*>(&Ut[pb][jb]);
+        const float4 uq = *reinterpret_cast<const float4*>(&Ut[qb][jb]);
+        const RotF rb = entry_rot(bpp, bqq, bpq);
+        if (d == 1) { Sn[pb][pb] = rb.napp; Sn[pb][qb] = rb.z; Sn[qb][qb] = rb.naqq; }
+        float4 po, qo;
+        po.x = rb.c * up.x + rb.s * uq.x; qo.x = rb.c * uq.x - rb.s * up.x;
+        po.y = rb.c * up.y + rb.s * uq.y; qo.y = rb.c * uq.y - rb.s * up.y;
+        po.z = rb.c * up.z + rb.s * uq.z; qo.z = rb.c * uq.z - rb.s * up.z;
+        po.w = rb.c * up.w + rb.s * uq.w; qo.w = rb.c * uq.w - rb.s * up.w;
+        *reinterpret_cast<float4*>(&Ut[pb][jb]) = po;
+        *reinterpret_cast<float4*>(&Ut[qb][jb]) = qo;
+      }
       __syncthreads();
       float(*t)[PL] = Sc;
       Sc = Sn;
@@ -398,7 +411,8 @@ __device__ __forceinline__ void solve_body_quads(float (*S)[Blk<PB>::PL], float 
       float so = 0.0f, sd = 0.0f;
       for (int e = tid; e < PM * PM; e += NT) {
         int i = e / PM, j = e % PM;
-        float v = Sc[i][j] * Sc[i][j];
+        float v = Sc[min(i, j)][max(i, j)];
+        v *= v;
         if (i == j) sd += v; else so += v;
       }
       for (int o = 32; o > 0; o >>= 1) { so += __shfl_xor(so, o); sd += __shfl_xor(sd, o); }
@@ -411,10 +425,10 @@ __device__ __forceinline__ void solve_body_quads(float (*S)[Blk<PB>::PL], float 
       prev_off = off;
     }
   }
-  if (Sc != S) {  // the result ends in S (callers read it there)
+  if (Sc != S) {  // the result ends in S (callers read its upper triangle there)
     for (int e = tid; e < PM * PM; e += NT) {
       int i = e / PM, j = e % PM;
-      S[i][j] = Sc[i][j];
+      if (i <= j) S[i][j] = Sc[i][j];
     }
     __syncthreads();
   }
@@ -814,13 +828,14 @@ __global__ void k_gather_q(const float* __restrict__ V, int n, int ldv, double* 
 
 // Block rows of the FP32 stage.  16 up to n = 32, where one 32 x 32 subproblem is the whole
 // matrix (n = 32: 0.56 against 0.96 ms with 32 rows); 32 up to n = 64, where one 64 x 64 is (n =
-// 48: 0.92 against 1.11 ms with 16), and above n = 2048, where the per-round passes over A and V
-// dominate and fewer rounds pay (n = 3000: 71 against 108 ms); 16 in between, where the
-// subproblem solves dominate (n = 1024: 16.1 against 19.5 ms, n = 2048: 35.5 against 39.0).
+// 48: 0.78 against 1.17 ms with 16), and above n = 1024, where the per-round passes over A and V
+// dominate and fewer rounds pay (n = 1439: 26.7 against 27.5 ms, 2048: 32.6 against 35.3, 4096:
+// 150 against 223); 16 in between, where the subproblem solves dominate (n = 512: 6.9 against
+// 8.0 ms, 1024: 15.7 against 16.0).
 // `request` 16 or 32 overrides the choice (0: automatic).
 static int block_rows(int n, int request) {
   if (request == 16 || request == 32) return request;
-  return ((n > 32 && n <= 64) || n > 2048) ? 32 : 16;
+  return ((n > 32 && n <= 64) || n > 1024) ? 32 : 16;
 }
 
 template <int PB>
