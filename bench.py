@@ -542,10 +542,8 @@ def bench_phases(args):
     out = {}
     probs = [("c2_n512", I.config_c2(n=512)), ("c2_n1024", I.config_c2()),
              ("c2_n2048", I.config_c2(n=2048)), ("c3_n4096", I.config_c3())]
-    names = {"one": ["wave reductions", "barrier", "cross-wave", "rescans", "parameters",
-                     "update"],
-             "many": ["local reductions", "publish + store acks", "barrier", "slot read + "
-                      "reduction", "parameters + row loads", "update"]}
+    names = ["best candidates, publish", "exchange", "selection + row loads", "rescans",
+             "parameters + entries", "proof, vote, stores, caches"]
     for name, prob in probs:
         n = prob.a.shape[0]
         a = torch.from_numpy(prob.a).to("cuda:0")
@@ -559,7 +557,7 @@ def bench_phases(args):
             out[key] = {"n": n, "workgroups": st["jacobi_wgs"], "rotations": st["rotations"],
                         "kernel_ms": st["ms_jacobi_kernel"],
                         "us_per_rotation": st["ms_jacobi_kernel"] * 1e3 / st["rotations"],
-                        "phase_ns_per_rotation": dict(zip(names[wgs], rp.stats["prof_ns"]))}
+                        "phase_ns_per_rotation": dict(zip(names, rp.stats["prof_ns"]))}
             log(f"{key}: {out[key]['us_per_rotation']:.2f} us/rotation")
     print(json.dumps({"workload": "FP64 Jacobi phase per rotation, one workgroup vs several",
                       "runs": out}), flush=True)

@@ -158,9 +158,12 @@ typedef struct je_stats {
                              /* events on `stream` around each launch)             */
   double a_hat_off;          /* off(A_hat) = sqrt(sum_{i != j} a_ij^2) of the matrix   */
                              /* the FP64 phase starts from (0 if not measured)       */
-  double prof_ns[6];         /* opts.profile: ns per rotation in the wave reductions,  */
-                             /* the barrier, the cross-wave reduction, row rescans,  */
-                             /* the rotation parameters and the row updates          */
+  double prof_ns[6];         /* opts.profile: ns per rotation in finding and publishing */
+                             /* the best candidates, the exchange, the selection and  */
+                             /* row loads, row rescans, the parameters and new        */
+                             /* entries, and the proof, vote, stores and caches (with */
+                             /* one rotation per exchange: wave reductions, barrier,  */
+                             /* cross-wave reduction, rescans, parameters, updates)   */
   float ms_apply_log;        /* applying the rotation log to V (HIP events on stream) */
   int scale_exp;             /* the input was scaled by 2^scale_exp (0: not scaled)   */
   int jacobi_wgs;            /* workgroups of the FP64 Jacobi kernel                  */
