@@ -145,9 +145,8 @@ def roofline(stats, n):
     achieved = per_rot * rot / (t * 1e-3) / 1e9 if t > 0 else 0.0
     half = 32.0 * n
     wgs = int(stats.get("jacobi_wgs", 1))
-    # the pivoted Jacobi kernel that ran: several one-wave workgroups (k_jacobi_mw) or one
-    # workgroup (k_jacobi)
-    kj = "k_jacobi_mw" if wgs > 1 else "k_jacobi"
+    # the pivoted Jacobi kernel that ran: several workgroups (four waves each up to n = 4096) or one
+    kj = ("k_jacobi_spec4" if n <= 4096 else "k_jacobi_spec_mw") if wgs > 1 else "k_jacobi"
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": pmc_traffic(PMC_FILE, "n", n),
