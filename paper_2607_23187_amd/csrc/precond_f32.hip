@@ -227,17 +227,6 @@ __device__ __forceinline__ void rot_block(const RotF& rb, const RotF& rc, bool d
   w = diag ? rb.naqq : rc.c * w1 - rc.s * z1;
 }
 
-// The rotation evaluated by lane `src` of this wave (cross-lane read, ds_bpermute).
-__device__ __forceinline__ RotF fetch_rot(const RotF& x, int src) {
-  RotF r;
-  r.c = __shfl(x.c, src);
-  r.s = __shfl(x.s, src);
-  r.napp = __shfl(x.napp, src);
-  r.naqq = __shfl(x.naqq, src);
-  r.z = __shfl(x.z, src);
-  return r;
-}
-
 // An inner round is one phase: the pairs of the round are disjoint, so J^T S J is, block by
 // block, X_bc -> J_b^T X_bc J_c over the 2 x 2 blocks of pair b's rows and pair c's columns.  S is
 // symmetric, so only one of X_bc and X_cb is formed, and only the upper triangle of S is kept.

@@ -10,7 +10,7 @@
 //
 // One persistent launch runs the whole rotation sequence: one workgroup with B in LDS when it
 // and the per-row state fit, several workgroups with a slice of B each above that, one
-// workgroup with B in HBM beyond what 32 slices hold.  With one workgroup, per rotation:
+// workgroup with B in HBM beyond what 32 slices hold.  The last of these, per rotation:
 //   argmax over the per-row best scores (each wave redundantly: no cross-wave exchange),
 //   rotation of columns p, q of B and of rows p, q of the right factor V^T, barrier,
 //   the dot products of rows p and q of A, barrier,
