@@ -22,6 +22,7 @@
 #include "jacobi_device.h"
 #include "kernels.h"
 #include "mw_exchange.h"
+#include "svd_columns.h"
 
 namespace je {
 
@@ -737,9 +738,12 @@ __global__ __launch_bounds__(NT) void k_svd1(const SDesc d) {
 
 // ------------------------------------------------------------------ several workgroups
 // B too large for one LDS: G workgroups on one XCD hold c columns of it each, in LDS for the
-// whole run.  A column-major copy of B in device memory carries the columns between them.
+// whole run.  Column-major copies of B in device memory carry the columns between them: two of
+// each column (svd_columns.h), since in a rotation the owners store the new columns p, q while
+// other workgroups may still load the old ones.
 // Per rotation every workgroup
-//   loads the old columns p, q (L2), rotates them into LDS (the owners also store them);
+//   loads the current copies of columns p, q (L2), rotates them into LDS (the owners also store
+//   them over the other copies);
 //   forms the dot products of its columns with the new p and q, one lane each in index order,
 //   and those of p and q with themselves;
 //   stores its entries of A (rows and columns p, q), refreshes the caches of its rows, rescans
@@ -857,6 +861,10 @@ __global__ __launch_bounds__(kSvdMwThreads) void k_svd_mw(const SDesc d, MwCtl* 
   int status = ST_OK, p = -1, q = -1;
   double vsel = -1.0;
   bool failed = false;
+  unsigned ver = 0;  // versions of the columns (svd_columns.h), the same in every wave
+  auto version = [&](int k) -> unsigned {
+    return (unsigned)readlane_i((int)ver, svd_version_lane(k)) & svd_version_bit(k);
+  };
   // this lane's part of the new rows p and q (wave 0)
   double vp = -1.0, ap = 0.0, vq = -1.0, aq = 0.0;
   int cp = INT_MAX, cq = INT_MAX;
@@ -930,8 +938,13 @@ __global__ __launch_bounds__(kSvdMwThreads) void k_svd_mw(const SDesc d, MwCtl* 
     q = max(s_rc[0], s_rc[1]);
     // ---- columns p, q: the loads first, the parameters overlap them
     const bool ownp = p >= k0 && p < k0 + nk, ownq = q >= k0 && q < k0 + nk;
-    double* gp = Yc + (size_t)p * ldc;
-    double* gq = Yc + (size_t)q * ldc;
+    const unsigned pv = version(p), qv = version(q);
+    const double* gp = Yc + svd_column_at(pv, p, n, ldc);
+    const double* gq = Yc + svd_column_at(qv, q, n, ldc);
+    double* newp = Yc + svd_column_at(!pv, p, n, ldc);
+    double* newq = Yc + svd_column_at(!qv, q, n, ldc);
+    if (lane == svd_version_lane(p)) ver ^= svd_version_bit(p);
+    if (lane == svd_version_lane(q)) ver ^= svd_version_bit(q);
     constexpr int kU = 4;
     double t = 0.0, cs = 1.0, sn = 0.0;
     for (int i0 = 0; i0 < m; i0 += kU * NT) {
@@ -982,9 +995,9 @@ __global__ __launch_bounds__(kSvdMwThreads) void k_svd_mw(const SDesc d, MwCtl* 
         }
       }
       if (ownp)
-        for (int i = lane; i < m; i += 64) st_ag(gp + i, colp[i]);
+        for (int i = lane; i < m; i += 64) st_ag(newp + i, colp[i]);
       if (ownq)
-        for (int i = lane; i < m; i += 64) st_ag(gq + i, colq[i]);
+        for (int i = lane; i < m; i += 64) st_ag(newq + i, colq[i]);
     }
     __syncthreads();
     // ---- entries of A, row caches (wave 0)
@@ -1192,7 +1205,7 @@ static bool svd_mw_shape(int m, int n, int* c, int* G) {
   if (n < 2 || svd_resident(m, n)) return false;
   *c = std::max(4, (n + kSvdMwGroups - 1) / kSvdMwGroups);
   *G = (n + *c - 1) / *c;
-  return svd_mw_lds(m, n, *c) + 1024 <= (size_t)svd_max_lds();
+  return n <= kSvdVersionCols && svd_mw_lds(m, n, *c) + 1024 <= (size_t)svd_max_lds();
 }
 
 static inline int svd_mw_ldc(int m) { return (m + 1) & ~1; }
@@ -1200,7 +1213,7 @@ static inline int svd_mw_ldc(int m) { return (m + 1) & ~1; }
 size_t svd_mw_bytes(int m, int n) {
   int c, G;
   if (!svd_mw_shape(m, n, &c, &G)) return 0;
-  return sizeof(MwCtl) + ((size_t)2 * G * kSvdMwWords + (size_t)n * svd_mw_ldc(m)) * 8;
+  return sizeof(MwCtl) + ((size_t)2 * G * kSvdMwWords + svd_column_doubles(n, svd_mw_ldc(m))) * 8;
 }
 
 template <int PIV>
@@ -1212,7 +1225,7 @@ static hipError_t svd_mw_t(const SDesc& d, MwCtl* mc, int c, int G, hipStream_t 
   double* xb = (double*)(mc + 1);
   double* Yc = xb + (size_t)2 * G * kSvdMwWords;
   const int ldc = svd_mw_ldc(d.m);
-  // Yc[k][i] = Y[i][k]
+  // Yc[k][i] = Y[i][k], the first copies
   hipLaunchKernelGGL(k_svd_columns, dim3((d.m + 31) / 32, (d.n + 31) / 32), dim3(256), 0, s, d.Y,
                      d.ldy, d.m, d.n, Yc, ldc);
   e = hipGetLastError();
