@@ -166,7 +166,8 @@ typedef struct je_stats {
                              /* cross-wave reduction, rescans, parameters, updates)   */
   float ms_apply_log;        /* applying the rotation log to V (HIP events on stream) */
   int scale_exp;             /* the input was scaled by 2^scale_exp (0: not scaled)   */
-  int jacobi_wgs;            /* workgroups of the FP64 Jacobi kernel                  */
+  int jacobi_wgs;            /* workgroups of the FP64 Jacobi kernel; SVD: those that  */
+                             /* hold B in their LDS, 0 when it stays in device memory */
 } je_stats;
 
 void je_opts_default(je_opts* opts);

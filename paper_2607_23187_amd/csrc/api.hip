@@ -623,6 +623,7 @@ int svd_one(const double* B, int m, int n, int ldb, double* S, double* U, int ld
     else if (mc.abort) return JE_ERR_DEVICE;
   }
   if (!multi) HIPCHK(launch_svd_jacobi(d, s));
+  Sx.jacobi_wgs = multi ? svd_mw_groups(m, n) : (svd_resident(m, n) ? 1 : 0);
   JCtl hc{};
   HIPCHK(hipMemcpyAsync(&hc, ctl, sizeof(JCtl), hipMemcpyDeviceToHost, s));
   Sx.ms_jacobi = tj.stop();

@@ -318,6 +318,7 @@ bool svd_resident(int m, int n);
 // whose misplaced and abort read as for launch_jacobi_mw.
 constexpr int kSvdMwGroups = 32;
 size_t svd_mw_bytes(int m, int n);
+int svd_mw_groups(int m, int n);  // its workgroups
 hipError_t launch_svd_mw(const SDesc& d, void* buf, hipStream_t s);
 int svd_mw_units(int m, int n);
 hipError_t launch_svd_out(const double* Y, int ldy, int m, const double* G, int ldg,

@@ -1216,6 +1216,11 @@ size_t svd_mw_bytes(int m, int n) {
   return sizeof(MwCtl) + ((size_t)2 * G * kSvdMwWords + svd_column_doubles(n, svd_mw_ldc(m))) * 8;
 }
 
+int svd_mw_groups(int m, int n) {
+  int c, G;
+  return svd_mw_shape(m, n, &c, &G) ? G : 0;
+}
+
 template <int PIV>
 static hipError_t svd_mw_t(const SDesc& d, MwCtl* mc, int c, int G, hipStream_t s) {
   hipLaunchKernelGGL(k_svd_rowbest<PIV>, dim3((d.n + 3) / 4), dim3(256), 0, s, d.G, d.ldg,
