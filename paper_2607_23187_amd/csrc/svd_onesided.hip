@@ -755,11 +755,15 @@ __global__ __launch_bounds__(NT) void k_svd1(const SDesc d) {
 constexpr int kSvdMwThreads = 256;
 constexpr int kSvdMwWords = 9;  // three candidates: score, entry, row << 32 | column
 
-// Row stride of the LDS columns: even (16-byte loads) and 4 banks apart from column to column.
-__host__ __device__ __forceinline__ int svd_mw_stride(int m) { return (m + 31) / 32 * 32 + 2; }
+// Row stride of the LDS columns: even (16-byte loads) and 4 banks apart from column to column
+// (no more than even for two or three columns, which meet in few banks in any case: 4066 x 3
+// still fits).
+__host__ __device__ __forceinline__ int svd_mw_stride(int m, int c) {
+  return c < 4 ? (m + 1) & ~1 : (m + 31) / 32 * 32 + 2;
+}
 
 __host__ __device__ __forceinline__ size_t svd_mw_lds(int m, int n, int c) {
-  return 8 * ((size_t)(c + 2) * svd_mw_stride(m) + n + 4 * (size_t)c) + 8 * (size_t)c;
+  return 8 * ((size_t)(c + 2) * svd_mw_stride(m, c) + n + 4 * (size_t)c) + 8 * (size_t)c;
 }
 
 // sum_i u_i y_i in index order, the operands of 8 terms in flight ahead of the sums.  What bounds
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(kSvdMwThreads) void k_svd_mw(const SDesc d, MwCtl* 
   __shared__ int s_cnt, s_ok, s_rc[3];
   __shared__ double s_best[3], s_val[3], s_new[2];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n = d.n, m = d.m, S = svd_mw_stride(m);
+  const int n = d.n, m = d.m, S = svd_mw_stride(m, c);
   const int k0 = g * c, nk = min(c, n - k0);
   const size_t ldg = d.ldg, ldv = d.ldv;
   double* Ys = smem;
@@ -1203,7 +1207,9 @@ hipError_t launch_svd_jacobi(const SDesc& d, hipStream_t s) {
 // one-workgroup resident kernel holds all of it.
 static bool svd_mw_shape(int m, int n, int* c, int* G) {
   if (n < 2 || svd_resident(m, n)) return false;
-  *c = std::max(4, (n + kSvdMwGroups - 1) / kSvdMwGroups);
+  // four columns at least; all of n <= 3, for the m at which one LDS holds them without the row
+  // caches of the resident kernel (4000 x 3: 0.74 ms a call, from device memory 1.2)
+  *c = std::min(n, std::max(4, (n + kSvdMwGroups - 1) / kSvdMwGroups));
   *G = (n + *c - 1) / *c;
   return n <= kSvdVersionCols && svd_mw_lds(m, n, *c) + 1024 <= (size_t)svd_max_lds();
 }

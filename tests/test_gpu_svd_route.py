@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 # B in device memory (both sides of the largest slice at n = 512)
 @pytest.mark.parametrize("m,n,wgs,cap", [
     (2, 2, 1, 100), (100, 100, 1, 300), (128, 128, 1, 300), (1500, 8, 1, 300),
-    (3300, 4, 1, 300), (4001, 4, 0, 100), (2500, 6, 2, 300), (130, 129, 26, 300), (512, 257, 29, 200),
+    (3953, 3, 1, 100), (3954, 3, 1, 100), (4066, 3, 1, 100), (4067, 3, 0, 100),
+    (4917, 2, 1, 100), (5001, 2, 1, 100), (3300, 4, 1, 300), (4001, 4, 0, 100), (2500, 6, 2, 300),
+    (130, 129, 26, 300), (512, 257, 29, 200),
     (700, 511, 32, 60), (1024, 512, 32, 60), (1088, 512, 32, 20), (1089, 512, 0, 20),
     (800, 768, 0, 20)])
 @pytest.mark.parametrize("precond", ["none", "fp32"])
