@@ -192,6 +192,10 @@ __device__ __forceinline__ bool wave_best_fast(double& v, int& k) {
 // Bytes of dynamic LDS of the resident mode: B by columns with an odd stride (the lanes' reads of
 // their own columns then fall in distinct banks), zeros, and rows p, q and the diagonal of A.
 constexpr int kSvdResMaxN = 128, kSvdResPad = 24;
+// Up to this n the kernel stores the entries of A that a rotation changes (KEEP); above it A is
+// formed once more at the end.  Few columns take few rotations, and forming A again is m dependent
+// sums of 22 ns: 4060 x 2 0.53 ms a call with it, 0.42 without (1000 x 8 1.48 and 1.45).
+constexpr int kSvdResKeepN = 8;
 // the rotated columns once more, with zeros up to the reads ahead of the last term
 __host__ __device__ __forceinline__ int svd_col_len(int m) { return ((m + 15) & ~15) + 8; }
 __host__ __device__ __forceinline__ int svd_lds_ld(int m) { return m | 1; }
@@ -283,7 +287,8 @@ __device__ __forceinline__ void svd_search2(double ep, double vp, double eq, dou
 // summed (13.3 ns a term; 24.7 with one block read, then summed; 17.6 with the rotated column
 // across the lanes, handed round by v_readlane).  The limit is one wave's LDS reads, 16 bytes a
 // lane in 21 cycles.  A itself is not kept: its entries are needed where they change and in the
-// rare rescan, which forms them again (same products, same order, same bits).
+// rare rescan, which forms them again (same products, same order, same bits); of up to kSvdResKeepN
+// columns they are stored as they change.
 //
 // Caches: lane k < 128 owns row k's: its exact best (score, column, entry), the second best, and a
 // bound of the others.  A row whose best moved down takes its second best or a new entry, where
@@ -297,7 +302,7 @@ __device__ __forceinline__ void svd_search2(double ep, double vp, double eq, dou
 // Hilbert factor of order 100 4.70 -> 3.96 us (dot products 1.4, parameters and columns 0.75,
 // scores 0.7, caches 0.3, selection 0.3, rescans 0.2), 130 x 100 5.0 -> 4.8, 500 x 30 10.3 -> 9.4,
 // 130 x 128 (on several workgroups before) 7.1 -> 4.9.
-template <int PIV>
+template <int PIV, bool KEEP>
 __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
   constexpr int NT = 256, kB = 8;
   extern __shared__ __attribute__((aligned(16))) double smem[];
@@ -517,6 +522,12 @@ __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
     ep = act && k != p ? score(dk, app, vp) : -1.0;
     eq = act && k != q ? score(dk, aqq, vq) : -1.0;
     moving = true;
+    if constexpr (KEEP) {
+      if (half == 0 && act) {
+        d.G[(size_t)p * d.ldg + k] = d.G[(size_t)k * d.ldg + p] = vp;
+        d.G[(size_t)q * d.ldg + k] = d.G[(size_t)k * d.ldg + q] = vq;
+      }
+    }
     if (tid == NT - 1) {
       diag[p] = app;
       diag[q] = aqq;
@@ -1186,7 +1197,9 @@ static hipError_t svd_jacobi_t(const SDesc& d, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (svd_resident(d.m, d.n)) {
-    e = svd_launch_main(k_svd_res<PIV>, 256, svd_lds_bytes(d.m, d.n), d, s);
+    const size_t sh = svd_lds_bytes(d.m, d.n);
+    if (d.n <= kSvdResKeepN) return svd_launch_main(k_svd_res<PIV, true>, 256, sh, d, s);
+    e = svd_launch_main(k_svd_res<PIV, false>, 256, sh, d, s);
     // A's entries once more, for the final off-norm and the singular values
     return e != hipSuccess ? e : launch_svd_gram(d.Y, d.ldy, d.m, d.n, d.G, d.ldg, s);
   }

@@ -56,3 +56,18 @@ def test_threads_keep_their_workgroups():
         t.join(60)
         assert not t.is_alive()
     assert out == [32, 32, 29, 29]
+
+
+# up to eight columns the entries of A are stored as they change, above that formed at the end
+@pytest.mark.parametrize("n", [2, 3, 5, 8, 9, 16])
+@pytest.mark.parametrize("cap", [1, 2, 7])
+def test_final_off_norm(n, cap):
+    m = 200
+    print(f"svd off-norm n={n} cap={cap}", flush=True)
+    g = J.svd(torch.from_numpy(I.svd_graded(m, n, seed=40 + n, decades=2.0)).to("cuda"),
+              max_rotations=cap)
+    b = (g.u * g.s).cpu().numpy()
+    a = b.T @ b
+    off = np.linalg.norm(a - np.diag(np.diag(a)))
+    # sums of m products on either side; U is B's columns divided by S, one rounding more
+    assert abs(g.stats["final_off"] - off) <= 4 * m * 2.0 ** -53 * np.linalg.norm(a)
