@@ -299,9 +299,10 @@ __device__ __forceinline__ void svd_search2(double ep, double vp, double eq, dou
 // the other row's cache.
 //
 // Measured, per rotation, before (A in LDS, a rescan for every best that moved down) and now:
-// Hilbert factor of order 100 4.70 -> 3.96 us (dot products 1.4, parameters and columns 0.75,
-// scores 0.7, caches 0.3, selection 0.3, rescans 0.2), 130 x 100 5.0 -> 4.8, 500 x 30 10.3 -> 9.4,
-// 130 x 128 (on several workgroups before) 7.1 -> 4.9.
+// Hilbert factor of order 100 4.70 -> 3.73 us (dot products 1.2, parameters and columns 0.75,
+// scores 0.7, caches 0.3, selection 0.3, rescans 0.2), 130 x 100 5.0 -> 4.4, 500 x 30 10.3 -> 8.9,
+// 130 x 128 (on several workgroups before) 7.1 -> 4.3.  Dot products of 16 terms at a time, with
+// up to 15 zeros at the end, took 4.0, 4.6, 9.5 and 4.5, and 33 x 16 6% longer than before.
 template <int PIV, bool KEEP>
 __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
   constexpr int NT = 256, kB = 8;
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
   const bool act = k < n;
   const double* mine = Yc + (act ? k : 0) * ldc;
   // sum_i u_i z_i in index order, z this lane's column, read a block of 8 ahead; the terms that
-  // fill up the last 16 have u_i = 0 and a finite z_i (the next column's, or the zeros behind
+  // fill up the last 8 have u_i = 0 and a finite z_i (the next column's, or the zeros behind
   // the last)
   auto dot = [&](const double* u) -> double {
     double x = 0.0, u0[kB], z0[kB], u1[kB], z1[kB];
@@ -342,8 +343,9 @@ __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
     for (int e = 0; e < kB; ++e) u0[e] = u[e];
 #pragma unroll
     for (int e = 0; e < kB; ++e) z0[e] = mine[e];
+    int i = 0;
 #pragma unroll 1
-    for (int i = 0; i < m; i += 2 * kB) {
+    for (; i + kB < m; i += 2 * kB) {
 #pragma unroll
       for (int e = 0; e < kB; ++e) u1[e] = u[i + kB + e];
 #pragma unroll
@@ -356,6 +358,10 @@ __global__ __launch_bounds__(256) void k_svd_res(const SDesc d) {
       for (int e = 0; e < kB; ++e) z0[e] = mine[i + 2 * kB + e];
 #pragma unroll
       for (int e = 0; e < kB; ++e) x += u1[e] * z1[e];
+    }
+    if (i < m) {
+#pragma unroll
+      for (int e = 0; e < kB; ++e) x += u0[e] * z0[e];
     }
     return x;
   };
