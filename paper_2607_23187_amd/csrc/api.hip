@@ -30,6 +30,10 @@ using namespace je;
 
 namespace {
 
+// One call of jacobi_eigh*, jacobi_svd or jacobi_eigh_batched* at a time, from its first launch to
+// the last wait on its stream: they share the workspace below, and launches whose workgroups wait
+// for each other (launch_jacobi_mw, launch_svd_mw) never meet with a part of theirs resident each.
+// The server's lanes run beside them; they launch nothing of that kind.
 std::mutex g_mu;
 
 struct Pool {
@@ -281,50 +285,6 @@ int precond_q(const double* Asym, int n, int ld, double*& X, double*& Xo, double
   return JE_OK;
 }
 
-// Turns of the launches whose workgroups wait for each other on one XCD.  All of a launch's
-// workgroups have to be resident together; several launches, each with a part of its own on the
-// XCD, would wait until their bounded waits run out and leave the work to the one-workgroup
-// kernels.  A caller's thread therefore takes the launch's share of the XCD (twelfths) before it
-// launches and gives it back once the launch has ended; shares go out in the order asked for.
-struct MwGate {
-  std::mutex mu;
-  std::condition_variable cv;
-  int used = 0;
-  unsigned long long next = 0, serving = 0;
-};
-constexpr int kGateDevices = 32;
-MwGate g_gate[kGateDevices];
-
-class MwTurn {
- public:
-  explicit MwTurn(int units) {
-    int dev = 0;
-    if (units <= 0 || hipGetDevice(&dev) != hipSuccess || dev < 0) return;
-    g_ = &g_gate[dev % kGateDevices];
-    units_ = units;
-    std::unique_lock<std::mutex> lk(g_->mu);
-    const unsigned long long mine = g_->next++;
-    g_->cv.wait(lk, [&] { return g_->serving == mine && g_->used + units_ <= kMwUnits; });
-    ++g_->serving;
-    g_->used += units_;
-    g_->cv.notify_all();
-  }
-  ~MwTurn() { end(); }
-  MwTurn(const MwTurn&) = delete;
-  MwTurn& operator=(const MwTurn&) = delete;
-  void end() {
-    if (!g_) return;
-    std::lock_guard<std::mutex> lk(g_->mu);
-    g_->used -= units_;
-    g_->cv.notify_all();
-    g_ = nullptr;
-  }
-
- private:
-  MwGate* g_ = nullptr;
-  int units_ = 0;
-};
-
 // One solve in the workspace at `base` (ws_bytes(n, precond, cap) bytes, device memory).
 int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, double tol,
               int pivot, int precond, const je_opts& o, je_stats* st, hipStream_t s,
@@ -427,7 +387,6 @@ int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, d
   float ms_apply = 0.f;
   float ms_kernel = 0.f;
   for (;;) {
-    MwTurn turn(multi ? jacobi_mw_units(n, pivot, o.stop) : 0);
     Timer tk(s);
     if (multi) HIPCHK(launch_jacobi_mw(d, base_rot, w.mw, s));
     else HIPCHK(launch_jacobi(d, base_rot, lds, mirror, s));
@@ -436,7 +395,6 @@ int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, d
     MwCtl mc{};
     if (multi) HIPCHK(hipMemcpyAsync(&mc, w.mw, 16, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    turn.end();
     if (multi && mc.misplaced) {
       // the workgroups were not all resident on one XCD: the state is untouched, the
       // one-workgroup kernel takes over
@@ -614,7 +572,6 @@ int svd_one(const double* B, int m, int n, int ldb, double* S, double* U, int ld
   bool multi = mw != nullptr;
   if (multi) {
     MwCtl mc{};
-    MwTurn turn(svd_mw_units(m, n));
     HIPCHK(launch_svd_mw(d, mw, s));
     HIPCHK(hipMemcpyAsync(&mc, mw, 16, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));

@@ -929,19 +929,6 @@ static hipError_t launch_mw_t(const JDesc& d, long long log_base, int G, MwCtl* 
   return hipGetLastError();
 }
 
-// Twelfths of an XCD (32 CUs) that a launch occupies while it runs: with four waves to a
-// workgroup a third of a CU's registers for each workgroup on it (its LDS, 8 n + 17 KB, is no
-// more), with one wave what its LDS takes, and half of a SIMD's registers at two rows a thread.
-int jacobi_mw_units(int n, int pivot, int stop) {
-  int G, RM;
-  const bool spec = jacobi_speculates(pivot, stop);
-  mw_shape(n, spec, &G, &RM);
-  const int per_cu = (G + 31) / 32;
-  if (spec && RM == 1) return 4 * per_cu;
-  const int lds = (int)((12 * (size_t)per_cu * (8 * (size_t)n + 1024) + 163839) / 163840);
-  return std::min(kMwUnits, std::max(RM == 1 ? 3 : 6, lds));
-}
-
 hipError_t launch_jacobi_mw(const JDesc& d, long long log_base, void* buf, hipStream_t s) {
   int G, RM;
   mw_shape(d.n, jacobi_speculates(d.pivot, d.stop), &G, &RM);

@@ -79,7 +79,6 @@ hipError_t launch_apply_log(double* V, int n, int ldv, const RotEntry* log, long
 // means the kernel returned without touching the state (run launch_jacobi instead);
 // abort = 1 without it means a wait ran out mid-run (device error).
 constexpr int kMwMaxGroups = 64;
-constexpr int kMwUnits = 12;  // see jacobi_mw_units
 struct alignas(8) MwCtl {
   int counter;                // arrivals at the exchange barriers
   int abort;                  // a wait ran out (read together with the counter)
@@ -93,7 +92,6 @@ struct alignas(8) MwCtl {
 void mw_shape(int n, bool spec, int* G, int* RM);
 size_t mw_bytes(int n);
 hipError_t launch_jacobi_mw(const JDesc& d, long long log_base, void* buf, hipStream_t s);
-int jacobi_mw_units(int n, int pivot, int stop);
 hipError_t launch_set_identity(double* V, int n, int ldv, hipStream_t s);
 // W[rank[k]] = 2^w_exp diag[k], Vout[:, rank[k]] = column k of Vw; rank ascending and
 // stable when sort != 0, else rank[k] = k.
@@ -320,7 +318,6 @@ constexpr int kSvdMwGroups = 32;
 size_t svd_mw_bytes(int m, int n);
 int svd_mw_groups(int m, int n);  // its workgroups
 hipError_t launch_svd_mw(const SDesc& d, void* buf, hipStream_t s);
-int svd_mw_units(int m, int n);
 hipError_t launch_svd_out(const double* Y, int ldy, int m, const double* G, int ldg,
                           const double* Vt, int ldvt, int n, int* rank, double* S, double* U,
                           int ldu, double* V, int ldv, hipStream_t s);

@@ -1271,14 +1271,6 @@ static hipError_t svd_mw_t(const SDesc& d, MwCtl* mc, int c, int G, hipStream_t 
   return hipGetLastError();
 }
 
-// Twelfths of an XCD that launch_svd_mw occupies: its LDS, a third for its registers at least.
-int svd_mw_units(int m, int n) {
-  int c, G;
-  if (!svd_mw_shape(m, n, &c, &G)) return 0;
-  const int lds = (int)((12 * (svd_mw_lds(m, n, c) + 1024) + 163839) / 163840);
-  return std::min(kMwUnits, std::max(4, lds));
-}
-
 hipError_t launch_svd_mw(const SDesc& d, void* buf, hipStream_t s) {
   int c, G;
   if (d.n > kSvdMaxN || !svd_mw_shape(d.m, d.n, &c, &G)) return hipErrorInvalidValue;
