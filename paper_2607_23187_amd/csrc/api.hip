@@ -377,7 +377,7 @@ int solve_one(const double* Au, int n, int lda, double* W, double* V, int ldv, d
   HIPCHK(launch_init_rows(d, s));
   const bool lds = jacobi_fits_lds(n);
   const bool mirror = o.update_mode != 2;  // one problem: mirror mode unless asked otherwise
-  // several workgroups for large HBM-resident problems (mirror mode, no phase timers)
+  // several workgroups for large HBM-resident problems (mirror mode)
   bool multi = !lds && mirror &&
                (o.jacobi_wgs == 2 ||
                 (o.jacobi_wgs == 0 &&

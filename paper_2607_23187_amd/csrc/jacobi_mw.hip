@@ -2,9 +2,16 @@
 // large matrix on several workgroups at once.
 //
 // The arithmetic, the pivot rule, the per-row caches of Sec. 3.2 and the mirrored storage
-// of A are those of the one-workgroup kernel (jacobi_kernels.hip); only the reductions are
-// spread out.  G workgroups of one wave each own the rows k = T + i G 64 (T = 64 g + lane,
-// i < RM).  Every rotation:
+// of A are those of the one-workgroup kernels (jacobi_wg.h); only the reductions are
+// spread out.  G workgroups own the rows k = T + i G 64 (T = 64 g + lane, i < RM).  Three
+// kernels:
+//   k_jacobi_spec4     several rotations per exchange, four waves per workgroup, one row per
+//                      lane (n <= 4096);
+//   k_jacobi_spec_mw   the same on one wave per workgroup, two rows per lane (n > 4096): the
+//                      loop of jacobi_spec.h;
+//   k_jacobi_mw        one rotation per exchange, one wave per workgroup, for the stop rules
+//                      that need more than the best pivot after each rotation.
+// The last of them, every rotation:
 //   1. each wave reduces its own candidates (best cached pivot over its rows, best entries
 //      of the new rows p and q of the last rotation) and publishes them in a slot of a
 //      double-buffered exchange area;
@@ -19,10 +26,14 @@
 // grid is 8 G and only workgroups with blockIdx % 8 == 0 work; they share XCD 0 and its
 // L2.  Loads of A and of the exchange area are relaxed agent-scope atomics (they miss the
 // per-CU cache and read L2), stores are workgroup-scope (acknowledged by that L2), and a
-// wave waits for its stores to be acknowledged before it arrives at a barrier.  A start barrier checks every workgroup's
-// XCC id: if they do not share one XCD (or a start wait runs out) the kernel returns
-// without touching the state and the host runs the one-workgroup kernel instead.  Every
-// wait is bounded; a wait that runs out sets an abort flag that ends all workgroups.
+// wave waits for its stores to be acknowledged before it arrives at a barrier.  Where a
+// round's stores may meet other workgroups' loads of the same round (entries between two of
+// its pivots' rows), the vote on the proven rotations comes between them: a workgroup votes
+// after its loads have returned and stores after all have voted.  A start barrier checks
+// every workgroup's XCC id: if they do not share one XCD (or a start wait runs out) the
+// kernel returns without touching the state and the host runs the one-workgroup kernel
+// instead.  Every wait is bounded; a wait that runs out sets an abort flag that ends all
+// workgroups.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -377,7 +388,6 @@ __global__ __launch_bounds__(64) void k_jacobi_mw(JDesc d, long long log_base, M
 // counter barrier, slot read), one on the vote.  The vote is a single 64-bit atomic per
 // workgroup, which carries the arrival and the first stage it could not prove: arrivals in
 // the low byte, seven bits per stage above it (at most 64 workgroups each).
-template <bool GAP_>
 struct MwExchange {
   static constexpr bool kExchange = true;
   static constexpr int kSlotWords = 2 * kMwMaxGroups * 4 * 4;  // two rounds, four a workgroup
@@ -496,7 +506,7 @@ __global__ __launch_bounds__(64) void k_jacobi_spec_mw(JDesc d, long long log_ba
   if (!mw_start(mc, G, g, round)) return;
   for (int l = lane; l < d.n; l += kWave) s_diag[l] = d.diag[l];
   __syncthreads();
-  MwExchange<GAP> ex{mc, xb, d.A, s_diag, G, g, g * kWave + lane, G * kWave, d.ld, lane,
+  MwExchange ex{mc, xb, d.A, s_diag, G, g, g * kWave + lane, G * kWave, d.ld, lane,
                      round, 0, true};
   spec_loop<RM, K, GAP>(d, log_base, ex);
 }
@@ -881,9 +891,9 @@ __global__ __launch_bounds__(256) void k_jacobi_spec4(JDesc d, long long log_bas
   }
 }
 
-// Workgroups and rows per thread for n: G = ceil(n / 64) one-wave workgroups, at most 32 (one
-// per CU of an XCD) for one rotation per exchange and 64 for speculative rounds, where the
-// scores of a round bound the wave; RM rows per thread (1, 2 or 4).
+// Workgroups and rows per lane for n: G = ceil(n / 64) workgroups, at most 32 (one per CU of
+// an XCD) for one rotation per exchange and 64 for speculative rounds, where the scores of a
+// round bound the wave; RM rows per lane (1, 2 or 4).
 void mw_shape(int n, bool spec, int* G, int* RM) {
   int g = (n + kWave - 1) / kWave;
   g = std::min(g, spec ? kMwMaxGroups : kMwMaxGroups / 2);

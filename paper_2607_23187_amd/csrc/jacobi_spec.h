@@ -108,7 +108,8 @@ __device__ __forceinline__ bool row_refresh(double& bs, int& ba, double& bu, int
 //   best(x)      exact best of the waves' row-scan candidates with the bound of the rest
 //   ld(r, k, tk), ld2(r, l), st(r, k, v), stm(k, r, v): entry (r, k) for an own row k, for any
 //                column l; row store, mirrored store
-//   diag(), set_diag(k, v, ts), row_ts
+//   diag(k), set_diag(p, q, dp, dq, ts): diagonal of A (ts: the rotation's number, for storage
+//                that chooses the newer copy of an entry by it)
 //   ok()         false after a wait ran out
 // All of them are called in uniform control flow of the wave.
 template <int RM, int K, bool GAP, class Ex>
