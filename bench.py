@@ -27,7 +27,8 @@ U = 2.0 ** -53
 HBM_PEAK_GBS = 8000.0
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2607_23187_amd", "csrc", f)
                for f in ("jacobi_kernels.hip", "jacobi_single.hip", "jacobi_queue.hip",
-                         "jacobi_mw.hip", "jacobi_wg.h", "jacobi_spec.h", "jacobi_device.h")]
+                         "jacobi_mw.hip", "mw_exchange.h", "jacobi_wg.h", "jacobi_spec.h",
+                         "jacobi_device.h")]
 PMC_FILE = os.path.join(ROOT, "profiles", "jacobi_kernel_c2_pmc.json")
 QUEUE_PMC_FILE = os.path.join(ROOT, "profiles", "jacobi_queue_c4_pmc.json")
 COUNTS_FILE = os.path.join(ROOT, "tests", "golden", "c2_oracle_counts.json")
