@@ -768,7 +768,7 @@ __global__ __launch_bounds__(NT) void k_svd1(const SDesc d) {
 //   exchanges its best row and those two, after which all hold the same winner.
 // Bound: the dot products (dot_in_order), then the exchange (0.6 us) and the L2 reads of the
 // columns and of the rows rescanned.  One workgroup alone read all of B from L2 at 22 GB/s per
-// rotation: 1024 x 512 186 -> 14.6 us per rotation, 300 x 260 38.8 -> 9, 130 x 129 13.4 -> 6.6.
+// rotation: 1024 x 512 186 -> 15 us per rotation, 300 x 260 38.8 -> 8.9, 130 x 129 13.4 -> 6.8.
 constexpr int kSvdMwThreads = 256;
 constexpr int kSvdMwWords = 9;  // three candidates: score, entry, row << 32 | column
 
